@@ -20,6 +20,7 @@
 #include "brick_geom.h"
 #include "chns_internal.h"
 #include "elem_chns.h"
+#include "pp_tile.h"
 
 namespace chns {
 namespace {
@@ -211,6 +212,7 @@ struct BrickArgs {
   const int32_t* hang;
   const uint8_t* wall;
   double alpha, beta;  // rho(phi) = alpha phi + beta
+  double ratio;        // rho-/rho+
   Phys phys;           // physical parameters of the CHNS forms
   double* partials;    // fused x.y partial per block, or null
   const int* done;
@@ -744,6 +746,94 @@ __device__ __forceinline__ uint32_t xcd_block() {
   return x * per + (x < rem ? x : rem) + b / kXcd;
 }
 
+// per-level folded constants of a form (see op_const)
+template <typename T>
+struct OpConst {
+  T A = 0, Bc = 0, Ms = 0, Am = 0, Bm = 0;
+};
+template <int DIM, typename T, int OP>
+__device__ __forceinline__ OpConst<T> op_const(const BrickArgs<T>& a, int lev) {
+  // per-level folded constants (powers of two are exact); FP32 fields carry
+  // 1 + phi, so rho = (beta - alpha) + alpha (1 + phi)
+  const double beta0 = sizeof(T) == 8 ? a.beta : a.beta - a.alpha;
+  OpConst<T> o;
+  if constexpr (OP == K_PPS) o.Ms = T(a.shift * ldexp(1.0, -(lev + 1) * DIM - 2 * DIM));
+  if constexpr (OP == K_VPS) {
+    // viscosity eta/(2 Re) = (gam phi + xi)/(2 Re) on the stiffness (folded
+    // like the pressure coefficient, without the reciprocal) and rho/dt on
+    // the mass
+    const int es = (lev + 1) * (DIM - 2) + 2 * DIM, em = -(lev + 1) * DIM - 2 * DIM;
+    const double g2 = a.phys.gam / (2.0 * a.phys.Re), x2 = a.phys.xi / (2.0 * a.phys.Re);
+    o.A = T(ldexp(g2, -es - DIM));
+    o.Bc = T(ldexp(sizeof(T) == 8 ? x2 : x2 - g2, -es));
+    o.Am = T(ldexp(a.alpha / a.phys.dt, em - DIM));
+    o.Bm = T(ldexp(beta0 / a.phys.dt, em));
+  }
+  if constexpr (OP == K_PP || OP == K_PPS) {
+    // c~ = detJ (2/h)^2 / 4^d / rho = 1 / (rho / K); K = 2^{-(lev+1)(d-2) - 2d}
+    const int e = (lev + 1) * (DIM - 2) + 2 * DIM;
+    o.A = T(ldexp(a.alpha, e - DIM));
+    o.Bc = T(ldexp(beta0, e));
+  } else if constexpr (OP == K_MASS) {
+    o.Bc = T(ldexp(1.0, -(lev + 1) * DIM - 2 * DIM));
+  } else if constexpr (OP == K_MASS_RHO) {
+    const int e = -(lev + 1) * DIM - 2 * DIM;
+    o.A = T(ldexp(a.alpha, e - DIM));
+    o.Bc = T(ldexp(beta0, e));
+  }
+  return o;
+}
+
+// One leaf of the form OP: corner values xc (inputs) and cc (coefficients),
+// or the accessor cv(f, a) for the heavy forms, to corner results ye.  The
+// momentum form instead hands each component's results to out(f, y) in turn.
+template <int DIM, typename T, int OP, class XC, class CC, class CV, class OUT>
+__device__ __forceinline__ void leaf_form(const BrickArgs<T>& a, const OpConst<T>& oc, int lev, const XC& xc,
+                                          const CC& cc, const CV& cv, const OUT& out,
+                                          T (*ye)[1 << DIM]) {
+  using TR = Traits<OP, DIM>;
+  constexpr int NI = TR::NI, NC = 1 << DIM;
+  // CHNS forms: physical gradient scale 2/h and det J = (h/2)^d
+  const double gs = ldexp(1.0, lev + 1), wdet = ldexp(1.0, -(lev + 1) * DIM);
+  if constexpr (OP == K_CH_JAC) {
+    el_chj<DIM, T>(cv, a.phys, lev, ye);
+  } else if constexpr (OP == K_VP) {
+    el_vp<DIM, T>(cv, a.phys, lev, out);
+  } else if constexpr (OP == K_PP || OP == K_PPS) {
+    elem_pp<DIM, T>(xc[0], cc[0], oc.A, oc.Bc, ye[0]);
+    if constexpr (OP == K_PPS) {
+      T r[NC], ym[NC];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) r[i] = oc.Ms;
+      elem_mass_apply<DIM, T>(xc[0], r, ym);
+#pragma unroll
+      for (int i = 0; i < NC; ++i) ye[0][i] += ym[i];
+    }
+  } else if constexpr (OP == K_VPS) {
+    elem_pp<DIM, T, false>(xc[0], cc[0], oc.A, oc.Bc, ye[0]);
+    T r[NC], ym[NC];
+    elem_mass_coef<DIM, T, true>(cc[0], oc.Am, oc.Bm, r);
+    elem_mass_apply<DIM, T>(xc[0], r, ym);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) ye[0][i] += ym[i];
+  } else if constexpr (OP == K_MASS || OP == K_MASS_RHO) {
+    T r[NC];
+    elem_mass_coef<DIM, T, OP == K_MASS_RHO>(cc[0], oc.A, oc.Bc, r);
+#pragma unroll
+    for (int f = 0; f < NI; ++f) elem_mass_apply<DIM, T>(xc[f], r, ye[f]);
+  } else if constexpr (OP == K_CH_RES) {
+    el_ch_res<DIM>(xc, cc, a.phys, gs, wdet, ye);
+  } else if constexpr (OP == K_VP_RHS) {
+    el_vp_rhs<DIM>(cc, a.phys, gs, wdet, ye);
+  } else if constexpr (OP == K_PP_RHS) {
+    el_pp_rhs<DIM>(cc, a.phys, gs, wdet, ye);
+  } else if constexpr (OP == K_VU_RHS) {
+    el_vu_rhs<DIM>(cc, a.phys, gs, wdet, ye);
+  } else {
+    el_energy<DIM>(cc, a.phys, gs, wdet, ye);
+  }
+}
+
 // One wavefront = BPB bricks; one lane = one leaf column of a brick, marching
 // along the last axis.  WHOLE: every node of the brick is gathered into LDS
 // up front (all loads in flight together); otherwise a three-layer LDS ring
@@ -765,6 +855,8 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
   // for them (the layer two ahead is stored after the barrier that ends the
   // reads of the layer it replaces) and leaves LDS for two waves per SIMD
   constexpr bool HEAVY = OP == K_VP || OP == K_CH_JAC;
+  // the 3D pressure form keeps its lower layer transformed (march.h)
+  constexpr bool MARCH = OP == K_PP && DIM == 3;
   constexpr int RING = WHOLE ? B + 1 : (HEAVY ? 2 : 3);
   __shared__ T lay[RING][BPB][NV][NL];
   // per-corner-type leaf contributions, indexed by the node they land on
@@ -875,36 +967,7 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
       v[f] = four ? (s01 + (v2 + v3)) * T(0.25) : s01 * T(0.5);
     }
   };
-  // per-level folded constants (powers of two are exact); FP32 fields carry
-  // 1 + phi, so rho = (beta - alpha) + alpha (1 + phi)
-  const double beta0 = sizeof(T) == 8 ? a.beta : a.beta - a.alpha;
-  T A = 0, Bc = 0, Ms = 0, Am = 0, Bm = 0;
-  if constexpr (OP == K_PPS) Ms = T(a.shift * ldexp(1.0, -(lev + 1) * DIM - 2 * DIM));
-  if constexpr (OP == K_VPS) {
-    // viscosity eta/(2 Re) = (gam phi + xi)/(2 Re) on the stiffness (folded
-    // like the pressure coefficient, without the reciprocal) and rho/dt on
-    // the mass
-    const int es = (lev + 1) * (DIM - 2) + 2 * DIM, em = -(lev + 1) * DIM - 2 * DIM;
-    const double g2 = a.phys.gam / (2.0 * a.phys.Re), x2 = a.phys.xi / (2.0 * a.phys.Re);
-    A = T(ldexp(g2, -es - DIM));
-    Bc = T(ldexp(sizeof(T) == 8 ? x2 : x2 - g2, -es));
-    Am = T(ldexp(a.alpha / a.phys.dt, em - DIM));
-    Bm = T(ldexp(beta0 / a.phys.dt, em));
-  }
-  if constexpr (OP == K_PP || OP == K_PPS) {
-    // c~ = detJ (2/h)^2 / 4^d / rho = 1 / (rho / K); K = 2^{-(lev+1)(d-2) - 2d}
-    const int e = (lev + 1) * (DIM - 2) + 2 * DIM;
-    A = T(ldexp(a.alpha, e - DIM));
-    Bc = T(ldexp(beta0, e));
-  } else if constexpr (OP == K_MASS) {
-    Bc = T(ldexp(1.0, -(lev + 1) * DIM - 2 * DIM));
-  } else if constexpr (OP == K_MASS_RHO) {
-    const int e = -(lev + 1) * DIM - 2 * DIM;
-    A = T(ldexp(a.alpha, e - DIM));
-    Bc = T(ldexp(beta0, e));
-  }
-  // CHNS forms: physical gradient scale 2/h and det J = (h/2)^d
-  const double gs = ldexp(1.0, lev + 1), wdet = ldexp(1.0, -(lev + 1) * DIM);
+  const OpConst<T> oc = op_const<DIM, T, OP>(a, lev);
 
   // -------- layered pipeline state (entries three layers ahead, values two)
   int64_t ent[KL];
@@ -1090,7 +1153,15 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
       for (int f = 0; f < NCF; ++f) cc[f][c + half * NH] = lay[buf][bl][NI + f][p];
     }
   };
-  if constexpr (!HEAVY) {
+  march::PpMarch<T> M;
+  march::PpCoef<T> pc{};
+  if constexpr (MARCH) {
+    pc = march::pp_coef3<T>(a.ratio, lev, march::pp_joint(a.ratio));
+    if (active) {
+      read_half(0, 1);
+      M.start(xc[0] + NH, cc[0] + NH);
+    }
+  } else if constexpr (!HEAVY) {
     if (active) read_half(0, 1);
   }
   constexpr int kUnroll = (OP == K_PP || OP == K_PPS || OP == K_VPS || OP == K_MASS) ? B : 1;
@@ -1099,7 +1170,10 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
     load_emit_entries(ez);
     if (active) {
       T ye[NO][NC];
-      if constexpr (!HEAVY) {
+      if constexpr (MARCH) {
+        read_half(ez + 1, 1);
+        M.step(xc[0] + NH, cc[0] + NH, pc, ye[0], [] {});
+      } else if constexpr (!HEAVY) {
 #pragma unroll
         for (int c = 0; c < NH; ++c) {
 #pragma unroll
@@ -1115,60 +1189,29 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
         const int p = (ix + bx) + (DIM == 3 ? (iy + by) * (B + 1) : 0);
         return lay[(ez + bz) % RING][bl][f][p];
       };
-      if constexpr (OP == K_CH_JAC) {
-        el_chj<DIM, T>(cv, a.phys, lev, ye);
-      } else if constexpr (OP == K_VP) {
+      if constexpr (!MARCH)
+      leaf_form<DIM, T, OP>(a, oc, lev, xc, cc, cv, [&](int f, const T* yf) {
         // each component's corner values go to the node accumulators as
         // soon as they are formed
-        el_vp<DIM, T>(cv, a.phys, lev, [&](int f, const T* yf) {
 #pragma unroll
-          for (int c = 0; c < NH; ++c) {
-            const int p = (ix + (c & 1)) + (DIM == 3 ? (iy + ((c >> 1) & 1)) * (B + 1) : 0);
-            accn[bl][f][c][p] = yf[c] + carry[f][c];
-            carry[f][c] = yf[c + NH];
-          }
-        });
-      } else if constexpr (OP == K_PP || OP == K_PPS) {
-        elem_pp<DIM, T>(xc[0], cc[0], A, Bc, ye[0]);
-        if constexpr (OP == K_PPS) {
-          T r[NC], ym[NC];
-#pragma unroll
-          for (int i = 0; i < NC; ++i) r[i] = Ms;
-          elem_mass_apply<DIM, T>(xc[0], r, ym);
-#pragma unroll
-          for (int i = 0; i < NC; ++i) ye[0][i] += ym[i];
+        for (int c = 0; c < NH; ++c) {
+          const int p = (ix + (c & 1)) + (DIM == 3 ? (iy + ((c >> 1) & 1)) * (B + 1) : 0);
+          accn[bl][f][c][p] = yf[c] + carry[f][c];
+          carry[f][c] = yf[c + NH];
         }
-      } else if constexpr (OP == K_VPS) {
-        elem_pp<DIM, T, false>(xc[0], cc[0], A, Bc, ye[0]);
-        T r[NC], ym[NC];
-        elem_mass_coef<DIM, T, true>(cc[0], Am, Bm, r);
-        elem_mass_apply<DIM, T>(xc[0], r, ym);
-#pragma unroll
-        for (int i = 0; i < NC; ++i) ye[0][i] += ym[i];
-      } else if constexpr (OP == K_MASS || OP == K_MASS_RHO) {
-        T r[NC];
-        elem_mass_coef<DIM, T, OP == K_MASS_RHO>(cc[0], A, Bc, r);
-#pragma unroll
-        for (int f = 0; f < NI; ++f) elem_mass_apply<DIM, T>(xc[f], r, ye[f]);
-      } else if constexpr (OP == K_CH_RES) {
-        el_ch_res<DIM>(xc, cc, a.phys, gs, wdet, ye);
-      } else if constexpr (OP == K_VP_RHS) {
-        el_vp_rhs<DIM>(cc, a.phys, gs, wdet, ye);
-      } else if constexpr (OP == K_PP_RHS) {
-        el_pp_rhs<DIM>(cc, a.phys, gs, wdet, ye);
-      } else if constexpr (OP == K_VU_RHS) {
-        el_vu_rhs<DIM>(cc, a.phys, gs, wdet, ye);
-      } else {
-        el_energy<DIM>(cc, a.phys, gs, wdet, ye);
-      }
+      }, ye);
       if constexpr (OP != K_VP) {
 #pragma unroll
         for (int f = 0; f < NO; ++f)
 #pragma unroll
           for (int c = 0; c < NH; ++c) {
             const int p = (ix + (c & 1)) + (DIM == 3 ? (iy + ((c >> 1) & 1)) * (B + 1) : 0);
-            accn[bl][f][c][p] = ye[f][c] + carry[f][c];
-            carry[f][c] = ye[f][c + NH];
+            if constexpr (MARCH) {
+              accn[bl][f][c][p] = ye[f][c];
+            } else {
+              accn[bl][f][c][p] = ye[f][c] + carry[f][c];
+              carry[f][c] = ye[f][c + NH];
+            }
           }
       }
     }
@@ -1186,6 +1229,7 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
   }
   load_emit_entries(B);
   if (active) {
+    if constexpr (MARCH) M.finish(carry[0]);
 #pragma unroll
     for (int f = 0; f < NO; ++f)
 #pragma unroll
@@ -1196,6 +1240,131 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
   }
   __syncthreads();
   emit_layer(B);
+  if (a.partials) {
+    dot = wave_sum(dot);
+    if (lane == 0) a.partials[blockIdx.x] = dot;
+  }
+}
+
+// Uniform, lexicographically numbered 2D meshes: every form in one kernel,
+// without shared-node slots and the combine pass.  These meshes are small
+// (4,225 nodes at 64 x 64) and a form's time is its launches and one chain of
+// dependent loads, so a second launch costs more than the leaves that two
+// waves compute twice here.
+//
+// A wave walks 64 leaf columns up a chunk of `own` node rows.  A lane
+// completes the nodes on its leaf's right side with the left-hand sums of the
+// next lane; the wave's last column is computed by the next wave as well
+// (64 columns give 63 nodes; the first wave also owns x = 0, the last the
+// right wall), and a chunk starts one leaf row below its first node row.
+constexpr int kTile2X = 63;
+template <typename T, int OP>
+__global__ __launch_bounds__(64) void k_tile2(BrickArgs<T> a, int tx, int own) {
+  using TR = Traits<OP, 2>;
+  constexpr int NI = TR::NI, NCF = TR::NCF, NO = TR::NO, NV = NI + NCF;
+  constexpr int NIa = NI > 0 ? NI : 1, NCa = NCF > 0 ? NCF : 1;
+  constexpr bool HEAVY = OP == K_VP || OP == K_CH_JAC;
+  if (a.done && *a.done) return;
+  const int lane = threadIdx.x, t = blockIdx.x % tx;
+  const int S = a.side;
+  const int64_t sy = S + 1;
+  const int cx = kTile2X * t + lane, q = min(cx, S - 1);
+  const bool leaf = cx < S;
+  const bool owner = leaf && (lane < kTile2X || cx == S - 1);
+  const int z0 = (int)(blockIdx.x / tx) * own, z1 = min(z0 + own, S + 1);
+  const int zb = max(z0 - 1, 0), ze = min(z1, S);
+  int lev = 0;
+  while ((1 << lev) < S) ++lev;
+  const OpConst<T> oc = op_const<2, T, OP>(a, lev);
+  auto on_wall = [&](int x, int z) { return x == 0 || x == S || z == 0 || z == S; };
+  // the two nodes of the lane's column in row z, wall nodes of a masked
+  // input read as zero
+  auto load = [&](int z, T (*v)[2]) {
+    const int64_t i = z * sy + q;
+#pragma unroll
+    for (int f = 0; f < NV; ++f) {
+      const T* src = f < NI ? a.x + f * a.n : a.cf[f < NI ? 0 : f - NI];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        v[f][c] = src[i + c];
+        if (f < NI && TR::MASK && on_wall(q + c, z)) v[f][c] = T(0);
+      }
+    }
+  };
+  double dot = 0.0;
+  auto put = [&](int x, int z, const T* v) {
+    const int64_t i = z * sy + x;
+#pragma unroll
+    for (int f = 0; f < NO; ++f) {
+      T w = v[f], xo = T(0);
+      if constexpr (NI == NO) {
+        if (TR::WALL == 1 || a.sm_r || a.partials) xo = (a.x + f * a.n)[i];
+      }
+      if (TR::WALL == 1 && on_wall(x, z)) w = xo;
+      if (TR::WALL == 2 && on_wall(x, z)) w = T(0);
+      if constexpr (OP == K_PP || OP == K_PPS || OP == K_VPS) {
+        if (a.sm_r) w = xo + a.sm_w * a.sm_d[i] * (a.sm_r[i] - w);
+      }
+      (a.y + f * a.n)[i] = w;
+      if constexpr (NI == NO && !HEAVY) {
+        if (a.partials) dot += (double)xo * (double)w;
+      }
+    }
+  };
+  T carry[NO][2], r[NO][2];
+  auto emit = [&](int z) {
+    T v[NO], l[NO];
+#pragma unroll
+    for (int f = 0; f < NO; ++f) {
+      l[f] = leaf ? r[f][0] : T(0);
+      const T next = __shfl_down(l[f], 1, 64);
+      v[f] = r[f][1] + (lane < 63 ? next : T(0));
+    }
+    if (owner) put(cx + 1, z, v);
+    if (cx == 0) put(0, z, l);
+  };
+  T lo[NV][2], hi[NV][2];
+  load(zb, lo);
+  load(zb + 1, hi);
+#pragma unroll
+  for (int f = 0; f < NO; ++f) carry[f][0] = carry[f][1] = T(0);
+  for (int z = zb; z < ze; ++z) {
+    T xc[NIa][4], cc[NCa][4], ye[NO][4];
+#pragma unroll
+    for (int f = 0; f < NV; ++f)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        if (f < NI) {
+          xc[f < NI ? f : 0][c] = lo[f][c];
+          xc[f < NI ? f : 0][c + 2] = hi[f][c];
+        } else {
+          cc[f < NI ? 0 : f - NI][c] = lo[f][c];
+          cc[f < NI ? 0 : f - NI][c + 2] = hi[f][c];
+        }
+        lo[f][c] = hi[f][c];
+      }
+    if (z + 1 < ze) load(z + 2, hi);
+    auto cv = [&](int f, int ca) -> T { return f < NI ? xc[f < NI ? f : 0][ca] : cc[f < NI ? 0 : f - NI][ca]; };
+    leaf_form<2, T, OP>(a, oc, lev, xc, cc, cv, [&](int f, const T* yf) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) ye[f][c] = yf[c];
+    }, ye);
+#pragma unroll
+    for (int f = 0; f < NO; ++f)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        r[f][c] = ye[f][c] + carry[f][c];
+        carry[f][c] = ye[f][c + 2];
+      }
+    if (z >= z0) emit(z);
+  }
+  if (z1 == S + 1) {
+#pragma unroll
+    for (int f = 0; f < NO; ++f)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) r[f][c] = carry[f][c];
+    emit(S);
+  }
   if (a.partials) {
     dot = wave_sum(dot);
     if (lane == 0) a.partials[blockIdx.x] = dot;
@@ -1365,6 +1534,36 @@ constexpr bool whole_fits() {
   return B <= 4 && (64 / LPB) * NL * (B + 1) * (TR::NI + TR::NCF) * (int)sizeof(T) <= 12 * 1024;
 }
 
+// The uniform-mesh kernels' chunk length: node rows (2D) or layers (3D) a
+// block completes.  A chunk costs one leaf row or layer more than it owns, so
+// long chunks do less work and short ones fill the chip; `fill` blocks are
+// enough (measured minimum of the chunk sweeps at 16 to 256 leaves per edge
+// in 3D, where chunks below three layers only pay while the chip is not full).
+int chunk_own(int64_t tiles, int side, int64_t fill, int least) {
+  if (tiles * (side + 1) <= fill / 3) return 1;
+  return (int)std::max<int64_t>(least, (tiles * (side + 1) + fill - 1) / fill);
+}
+
+// 3D pressure operator on a uniform mesh: arguments of k_pp_tile
+template <typename T>
+TileArgs<T> tile3_args(const BrickArgs<T>& b, int level) {
+  TileArgs<T> t{};
+  t.x = b.x;
+  t.phi = b.cf[0];
+  t.y = b.y;
+  t.ratio = b.ratio;
+  t.joint = march::pp_joint(b.ratio);
+  t.level = level;
+  t.sm_r = b.sm_r;
+  t.sm_d = b.sm_d;
+  t.sm_w = b.sm_w;
+  t.partials = b.partials;
+  t.done = b.done;
+  tile_geometry(t, b.side, 1);
+  tile_geometry(t, b.side, chunk_own((int64_t)t.tx * t.ty, b.side, 1536, 3));
+  return t;
+}
+
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 void launch_one(int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
   const dim3 g((unsigned)grid), blk(64);
@@ -1372,7 +1571,8 @@ void launch_one(int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
   // the scalar momentum form (viscous stiffness and density mass together)
   // needs ~140 registers: capped at four waves it spilled (88 bytes per lane
   // on table bricks), uncapped it runs three without
-  if constexpr (OP == K_PP || OP == K_PPS || OP == K_MASS)
+  // (the pressure march on 8^3 FP64 bricks needs ~134 too: three waves)
+  if constexpr ((OP == K_PP && !(DIM == 3 && B == 8 && sizeof(T) == 8)) || OP == K_PPS || OP == K_MASS)
     k_brick_o4<DIM, B, T, OP, W, STRUCT><<<g, blk, 0, s>>>(a);
   else if constexpr (OP == K_CH_JAC && DIM == 3 && B == 8 && STRUCT && sizeof(T) == 8)
     k_brick_o2<DIM, B, T, OP, W, STRUCT><<<g, blk, 0, s>>>(a);
@@ -1407,7 +1607,7 @@ int launch_bricks(const DevMesh& dm, BrickArgs<T> a, hipStream_t s, int& part_of
     if (part) a.partials = part + part_off;
     if (dm.structured) {
       a.anchor = bc.anchor;
-      launch_b<DIM, T, OP, true>(bc.B, grid, s, a);
+      if constexpr (DIM == 3 && !(OP == K_PP && sizeof(T) == 8)) launch_b<DIM, T, OP, true>(bc.B, grid, s, a);
     } else {
       launch_b<DIM, T, OP, false>(bc.B, grid, s, a);
     }
@@ -1482,6 +1682,7 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   a.phys = phys_of(c.prm);
   a.alpha = a.phys.alpha;
   a.beta = a.phys.beta;
+  a.ratio = c.prm.rho_minus / c.prm.rho_plus;
   a.partials = o.fuse_dot ? c.partials : nullptr;
   a.done = o.done;
   a.sm_r = (const T*)o.sm_r;
@@ -1494,17 +1695,45 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   int part_off = 0;
   const char* tag = op_tag(OP, sizeof(T) == 8);
   hipEvent_t ev;
-  c.prof_begin(tag, s, &ev);
-  int rc = launch_bricks<DIM, T, OP>(dm, a, s, part_off);
-  if (rc) return rc;
+  // uniform meshes in one kernel, no slots and no combine: every 2D form and
+  // the 3D pressure operator in FP64.  In FP32 that operator keeps the bricks
+  // and their order of sums, so that it gives the same bits as the brick path
+  // of an octree with the same leaves: refinement around restarted FP32 solves
+  // turns a change of rounding into a few iterations (327 to 338 for the
+  // learned preconditioner at 128^3), and the two paths agree exactly.
+  bool whole = false;
+  if (dm.structured) {
+    if constexpr (DIM == 2) {
+      const int tx = std::max(1, (dm.side - 1 + kTile2X - 1) / kTile2X);
+      const int own = chunk_own(tx, dm.side, 6144, 2);
+      part_off = tx * ((dm.side + own) / own);
+      c.prof_begin(tag, s, &ev);
+      k_tile2<T, OP><<<dim3((unsigned)part_off), dim3(64), 0, s>>>(a, tx, own);
+      whole = true;
+    } else if constexpr (OP == K_PP && sizeof(T) == 8) {
+      const TileArgs<T> t = tile3_args<T>(a, dm.max_level);
+      part_off = t.blocks();
+      c.prof_begin(tag, s, &ev);
+      if (t.sm_r) k_pp_tile<T, true><<<dim3((unsigned)part_off), dim3(256), 0, s>>>(t);
+      else k_pp_tile<T, false><<<dim3((unsigned)part_off), dim3(256), 0, s>>>(t);
+      whole = true;
+    }
+  }
+  if (whole) {
+    CHNS_HIP(hipGetLastError());
+  } else {
+    c.prof_begin(tag, s, &ev);
+    int rc = launch_bricks<DIM, T, OP>(dm, a, s, part_off);
+    if (rc) return rc;
+  }
   c.prof_end(tag, s, ev);
-  const int64_t cb = combine_blocks(dm);
+  const int64_t cb = whole ? 0 : combine_blocks(dm);
   const int total = part_off + (int)cb;
   if (o.fuse_dot && total > kMaxPartials) {
     set_error("mesh needs more reduction partials than allocated");
     return CHNS_EINVAL;
   }
-  if (cb > 0 || o.fuse_dot) {
+  if (!whole && (cb > 0 || o.fuse_dot)) {
     const unsigned g = (unsigned)(cb > 0 ? cb : 1);
     c.prof_begin("combine", s, &ev);
     k_combine<T, TR::NO, TR::WALL><<<dim3(g), dim3(256), 0, s>>>(
