@@ -739,9 +739,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 // curve, so handing XCD x the contiguous run of brick groups
 // [start(x), start(x) + count(x)) keeps the node layers that neighbouring
 // bricks share in one L2.  A bijection for any grid size.
-__device__ __forceinline__ uint32_t xcd_block() {
+__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t g) {
   constexpr uint32_t kXcd = 8;
-  const uint32_t g = gridDim.x, b = blockIdx.x;
   const uint32_t per = g / kXcd, rem = g % kXcd, x = b % kXcd;
   return x * per + (x < rem ? x : rem) + b / kXcd;
 }
@@ -834,6 +833,47 @@ __device__ __forceinline__ void leaf_form(const BrickArgs<T>& a, const OpConst<T
   }
 }
 
+// Table meshes, every field of node entry e in two passes: first one load
+// per field with no branch (a hanging node reads node 0 as a placeholder),
+// so that all of them are in flight together; then, only in waves that
+// hold a hanging node, its fields replaced by the mean of its parents
+// (edge: (a + b) / 2, face: ((a + b) + (c + d)) / 4).
+template <int DIM, typename T, int OP>
+__device__ __forceinline__ void table_first(const BrickArgs<T>& a, int32_t e, T* v) {
+  using TR = Traits<OP, DIM>;
+  const int32_t i = e >= 0 ? e : 0;
+#pragma unroll
+  for (int f = 0; f < TR::NI + TR::NCF; ++f)
+    v[f] = f < TR::NI ? fetch<T, TR::MASK>(a.x + f * a.n, a.wall, i) : a.cf[f - TR::NI][i];
+}
+template <int DIM, typename T, int OP>
+__device__ __forceinline__ void table_parents(const BrickArgs<T>& a, int32_t e, T* v) {
+  using TR = Traits<OP, DIM>;
+  const int32_t* hp = a.hang + 4 * (int64_t)(-e - 1);
+  const int32_t p0 = hp[0], p1 = hp[1], p2 = hp[2], p3 = hp[3];
+  const bool four = p2 >= 0;
+  const int32_t q2 = four ? p2 : p0, q3 = four ? p3 : p1;
+#pragma unroll
+  for (int f = 0; f < TR::NI + TR::NCF; ++f) {
+    T v0, v1, v2, v3;
+    if (f < TR::NI) {
+      const T* src = a.x + f * a.n;
+      v0 = fetch<T, TR::MASK>(src, a.wall, p0);
+      v1 = fetch<T, TR::MASK>(src, a.wall, p1);
+      v2 = fetch<T, TR::MASK>(src, a.wall, q2);
+      v3 = fetch<T, TR::MASK>(src, a.wall, q3);
+    } else {
+      const T* src = a.cf[f - TR::NI];
+      v0 = src[p0];
+      v1 = src[p1];
+      v2 = src[q2];
+      v3 = src[q3];
+    }
+    const T s01 = v0 + v1;
+    v[f] = four ? (s01 + (v2 + v3)) * T(0.25) : s01 * T(0.5);
+  }
+}
+
 // One wavefront = BPB bricks; one lane = one leaf column of a brick, marching
 // along the last axis.  WHOLE: every node of the brick is gathered into LDS
 // up front (all loads in flight together); otherwise a three-layer LDS ring
@@ -841,30 +881,44 @@ __device__ __forceinline__ void leaf_form(const BrickArgs<T>& a, const OpConst<T
 // lexicographic node numbers, 32-bit offsets computed from the brick anchor.
 // The layer march is unrolled for the small scalar forms (pressure, mass):
 // ring slots, carries and node offsets become constants.
-template <int DIM, int B, typename T, int OP, bool WHOLE, bool STRUCT>
-__device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
+template <int DIM, int B, typename T, int OP, bool WHOLE>
+struct BrickShm {
   using TR = Traits<OP, DIM>;
-  constexpr int NI = TR::NI, NCF = TR::NCF, NO = TR::NO, NV = NI + NCF;
-  constexpr int NIa = NI > 0 ? NI : 1, NCa = NCF > 0 ? NCF : 1;
-  constexpr int LPB = DIM == 3 ? B * B : B;  // lanes (leaf columns) per brick
-  constexpr int BPB = 64 / LPB;              // bricks per wavefront
-  constexpr int NL = DIM == 3 ? (B + 1) * (B + 1) : (B + 1);  // nodes per layer
-  constexpr int KL = (NL + LPB - 1) / LPB;   // layer nodes handled per lane
-  constexpr int NC = 1 << DIM, NH = NC / 2;
+  static constexpr int NV = TR::NI + TR::NCF;
+  static constexpr int LPB = DIM == 3 ? B * B : B;  // lanes (leaf columns) per brick
+  static constexpr int BPB = 64 / LPB;              // bricks per wavefront
+  static constexpr int NL = DIM == 3 ? (B + 1) * (B + 1) : (B + 1);  // nodes per layer
+  static constexpr int NH = (1 << DIM) / 2;
   // heavy forms read corners from LDS on demand; a two-layer ring suffices
   // for them (the layer two ahead is stored after the barrier that ends the
   // reads of the layer it replaces) and leaves LDS for two waves per SIMD
-  constexpr bool HEAVY = OP == K_VP || OP == K_CH_JAC;
-  // the 3D pressure form keeps its lower layer transformed (march.h)
-  constexpr bool MARCH = OP == K_PP && DIM == 3;
-  constexpr int RING = WHOLE ? B + 1 : (HEAVY ? 2 : 3);
-  __shared__ T lay[RING][BPB][NV][NL];
+  static constexpr bool HEAVY = OP == K_VP || OP == K_CH_JAC;
+  static constexpr int RING = WHOLE ? B + 1 : (HEAVY ? 2 : 3);
+  T lay[RING][BPB][NV][NL];
   // per-corner-type leaf contributions, indexed by the node they land on
   // (zero where no leaf of the brick lands): a node sums NH entries
-  __shared__ T accn[BPB][NO][NH][NL];
+  T accn[BPB][TR::NO][NH][NL];
+};
+
+template <int DIM, int B, typename T, int OP, bool WHOLE, bool STRUCT>
+__device__ __forceinline__ void brick_body(const BrickArgs<T>& a, BrickShm<DIM, B, T, OP, WHOLE>& sm, uint32_t block,
+                                           uint32_t grid) {
+  using TR = Traits<OP, DIM>;
+  using SH = BrickShm<DIM, B, T, OP, WHOLE>;
+  constexpr int NI = TR::NI, NCF = TR::NCF, NO = TR::NO, NV = NI + NCF;
+  constexpr int NIa = NI > 0 ? NI : 1, NCa = NCF > 0 ? NCF : 1;
+  constexpr int LPB = SH::LPB, BPB = SH::BPB, NL = SH::NL;
+  constexpr int KL = (NL + LPB - 1) / LPB;   // layer nodes handled per lane
+  constexpr int NC = 1 << DIM, NH = NC / 2;
+  constexpr bool HEAVY = SH::HEAVY;
+  constexpr int RING = SH::RING;
+  // the 3D pressure form keeps its lower layer transformed (march.h)
+  constexpr bool MARCH = OP == K_PP && DIM == 3;
+  auto& lay = sm.lay;
+  auto& accn = sm.accn;
   if (a.done && *a.done) return;
   const int lane = threadIdx.x, bl = lane / LPB, ll = lane % LPB;
-  const int64_t brick = (int64_t)xcd_block() * BPB + bl;
+  const int64_t brick = (int64_t)xcd_block(block, grid) * BPB + bl;
   const bool active = brick < a.count;
   const int ix = ll % B, iy = DIM == 3 ? ll / B : 0;
   const int32_t* tab = a.table + (active ? brick : 0) * (int64_t)(NL * (B + 1));
@@ -932,41 +986,8 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
     }
     return a.cf[f - NI][(int32_t)e];
   };
-  // Table meshes, every field of node entry e in two passes: first one load
-  // per field with no branch (a hanging node reads node 0 as a placeholder),
-  // so that all of them are in flight together; then, only in waves that
-  // hold a hanging node, its fields replaced by the mean of its parents
-  // (edge: (a + b) / 2, face: ((a + b) + (c + d)) / 4).
-  auto table_vals = [&](int32_t e, T* v) {
-    const int32_t i = e >= 0 ? e : 0;
-#pragma unroll
-    for (int f = 0; f < NV; ++f) v[f] = f < NI ? fetch<T, TR::MASK>(a.x + f * a.n, a.wall, i) : a.cf[f - NI][i];
-  };
-  auto table_hang = [&](int32_t e, T* v) {
-    const int32_t* hp = a.hang + 4 * (int64_t)(-e - 1);
-    const int32_t p0 = hp[0], p1 = hp[1], p2 = hp[2], p3 = hp[3];
-    const bool four = p2 >= 0;
-    const int32_t q2 = four ? p2 : p0, q3 = four ? p3 : p1;
-#pragma unroll
-    for (int f = 0; f < NV; ++f) {
-      T v0, v1, v2, v3;
-      if (f < NI) {
-        const T* src = a.x + f * a.n;
-        v0 = fetch<T, TR::MASK>(src, a.wall, p0);
-        v1 = fetch<T, TR::MASK>(src, a.wall, p1);
-        v2 = fetch<T, TR::MASK>(src, a.wall, q2);
-        v3 = fetch<T, TR::MASK>(src, a.wall, q3);
-      } else {
-        const T* src = a.cf[f - NI];
-        v0 = src[p0];
-        v1 = src[p1];
-        v2 = src[q2];
-        v3 = src[q3];
-      }
-      const T s01 = v0 + v1;
-      v[f] = four ? (s01 + (v2 + v3)) * T(0.25) : s01 * T(0.5);
-    }
-  };
+  auto table_vals = [&](int32_t e, T* v) { table_first<DIM, T, OP>(a, e, v); };
+  auto table_hang = [&](int32_t e, T* v) { table_parents<DIM, T, OP>(a, e, v); };
   const OpConst<T> oc = op_const<DIM, T, OP>(a, lev);
 
   // -------- layered pipeline state (entries three layers ahead, values two)
@@ -1242,7 +1263,7 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a) {
   emit_layer(B);
   if (a.partials) {
     dot = wave_sum(dot);
-    if (lane == 0) a.partials[blockIdx.x] = dot;
+    if (lane == 0) a.partials[block] = dot;
   }
 }
 
@@ -1371,24 +1392,152 @@ __global__ __launch_bounds__(64) void k_tile2(BrickArgs<T> a, int tx, int own) {
   }
 }
 
-template <int DIM, int B, typename T, int OP, bool WHOLE, bool STRUCT>
+template <int DIM, int B, typename T, int OP>
+constexpr bool whole_fits() {
+  using TR = Traits<OP, DIM>;
+  constexpr int LPB = DIM == 3 ? B * B : B;
+  constexpr int NL = DIM == 3 ? (B + 1) * (B + 1) : (B + 1);
+  // deep bricks keep the three-layer ring (better occupancy, loads pipelined)
+  return B <= 4 && (64 / LPB) * NL * (B + 1) * (TR::NI + TR::NCF) * (int)sizeof(T) <= 12 * 1024;
+}
+template <int DIM, int B, typename T, int OP>
+using ShmOf = BrickShm<DIM, B, T, OP, whole_fits<DIM, B, T, OP>()>;
+
+template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) void k_brick(BrickArgs<T> a) {
-  brick_body<DIM, B, T, OP, WHOLE, STRUCT>(a);
+  __shared__ ShmOf<DIM, B, T, OP> sm;
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT>(a, sm, blockIdx.x, gridDim.x);
 }
 // the pressure and mass forms (at most 128 VGPRs in FP64): capped at four
 // waves per SIMD, which keeps the FP32 instances from trading their latency
 // hiding for occupancy
-template <int DIM, int B, typename T, int OP, bool WHOLE, bool STRUCT>
+template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_brick_o4(BrickArgs<T> a) {
-  brick_body<DIM, B, T, OP, WHOLE, STRUCT>(a);
+  __shared__ ShmOf<DIM, B, T, OP> sm;
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT>(a, sm, blockIdx.x, gridDim.x);
 }
 // the FP64 3D Cahn-Hilliard Jacobian on structured 8^3 bricks: its LDS
 // admits three waves per SIMD, which at 128^3 leaves a third of the bricks
 // to a second, sparse round; held to two waves it runs two full rounds
 // (0.095 -> 0.090 ms; equal at 256^3; on adaptive meshes three are faster)
-template <int DIM, int B, typename T, int OP, bool WHOLE, bool STRUCT>
+template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_brick_o2(BrickArgs<T> a) {
-  brick_body<DIM, B, T, OP, WHOLE, STRUCT>(a);
+  __shared__ ShmOf<DIM, B, T, OP> sm;
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT>(a, sm, blockIdx.x, gridDim.x);
+}
+
+// Single leaves (bricks of one) of a table mesh: one lane per leaf, its
+// corners in registers, its results straight to its slots; no LDS.
+template <int DIM, typename T, int OP>
+__device__ __forceinline__ void single_body(const BrickArgs<T>& a, uint32_t block, uint32_t grid) {
+  using TR = Traits<OP, DIM>;
+  constexpr int NI = TR::NI, NCF = TR::NCF, NO = TR::NO, NV = NI + NCF;
+  constexpr int NIa = NI > 0 ? NI : 1, NCa = NCF > 0 ? NCF : 1, NC = 1 << DIM;
+  const int64_t leaf = (int64_t)xcd_block(block, grid) * 64 + threadIdx.x;
+  // every node of a single leaf goes through the combine: no fused dot here
+  if (a.partials && threadIdx.x == 0) a.partials[block] = 0.0;
+  if (leaf >= a.count) return;
+  const int lev = a.level[leaf];
+  int32_t e[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) e[c] = a.table[leaf * NC + c];
+  T v[NC][NV];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) table_first<DIM, T, OP>(a, e[c], v[c]);
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    if (e[c] < 0) table_parents<DIM, T, OP>(a, e[c], v[c]);
+  T xc[NIa][NC], cc[NCa][NC], ye[NO][NC];
+#pragma unroll
+  for (int f = 0; f < NV; ++f)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      if (f < NI) xc[f < NI ? f : 0][c] = v[c][f];
+      else cc[f < NI ? 0 : f - NI][c] = v[c][f];
+    }
+  if constexpr (OP == K_PP && DIM == 3) {
+    march::PpMarch<T> M;
+    M.start(xc[0], cc[0]);
+    M.step(xc[0] + 4, cc[0] + 4, march::pp_coef3<T>(a.ratio, lev, march::pp_joint(a.ratio)), ye[0], [] {});
+    M.finish(ye[0] + 4);
+  } else {
+    auto cv = [&](int f, int ca) -> T { return f < NI ? xc[f < NI ? f : 0][ca] : cc[f < NI ? 0 : f - NI][ca]; };
+    leaf_form<DIM, T, OP>(a, op_const<DIM, T, OP>(a, lev), lev, xc, cc, cv, [&](int f, const T* yf) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) ye[f][c] = yf[c];
+    }, ye);
+  }
+#pragma unroll
+  for (int f = 0; f < NO; ++f)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int64_t sl = a.slot_base + leaf * a.nbnd + brick_rank(DIM, 1, c & 1, DIM == 3 ? (c >> 1) & 1 : 0, c >> (DIM - 1));
+      a.slots[f * a.n_slots + sl] = ye[f][c];
+    }
+}
+
+// Table meshes: every brick class in one launch, the largest bricks first.
+// An octree around an interface has a few thousand waves of each class or
+// less (levels 5-8: 1,248 of 4^3, 600 of 2^3 and 156 of single leaves for
+// 1,024 SIMDs), so launched one after another each leaves most of the chip
+// idle and its own tail exposed.  Each class starts at a multiple of eight
+// blocks, which keeps its XCD order.  Four launches -> one: FP32 pressure
+// apply at levels 5-9 82.8 -> 57.1 us, multigrid solve at levels 5-8 10.25 ->
+// 7.97 ms, rising-bubble step at levels 5-8 212 -> 161 ms.
+struct ClassArgs {
+  const int32_t* table;
+  const int32_t* abase;
+  const int8_t* level;
+  int64_t count, slot_base;
+  int nbnd;
+  uint32_t first, grid;  // its blocks
+};
+struct ClassTable {
+  ClassArgs c[kBrickClasses];  // edge 8, 4, 2, 1
+};
+template <int DIM, typename T, int OP, bool EIGHT>
+__device__ __forceinline__ void bricks_body(BrickArgs<T> a, const ClassTable& t) {
+  constexpr size_t kShm = std::max({EIGHT ? sizeof(ShmOf<DIM, 8, T, OP>) : 0, sizeof(ShmOf<DIM, 4, T, OP>),
+                                    sizeof(ShmOf<DIM, 2, T, OP>)});
+  __shared__ __align__(16) unsigned char raw[kShm];
+  if (a.done && *a.done) return;
+  const uint32_t b = blockIdx.x;
+  auto take = [&](int k) {
+    const ClassArgs& c = t.c[k];
+    a.table = c.table;
+    a.abase = c.abase;
+    a.level = c.level;
+    a.count = c.count;
+    a.slot_base = c.slot_base;
+    a.nbnd = c.nbnd;
+    if (a.partials) a.partials += c.first;
+    return b - c.first;
+  };
+  if (EIGHT && b < t.c[0].first + t.c[0].grid) {
+    if constexpr (EIGHT) {
+      const uint32_t i = take(0);
+      brick_body<DIM, 8, T, OP, whole_fits<DIM, 8, T, OP>(), false>(a, *(ShmOf<DIM, 8, T, OP>*)raw, i, t.c[0].grid);
+    }
+  } else if (b < t.c[1].first + t.c[1].grid) {
+    const uint32_t i = take(1);
+    brick_body<DIM, 4, T, OP, whole_fits<DIM, 4, T, OP>(), false>(a, *(ShmOf<DIM, 4, T, OP>*)raw, i, t.c[1].grid);
+  } else if (b < t.c[2].first + t.c[2].grid) {
+    const uint32_t i = take(2);
+    brick_body<DIM, 2, T, OP, whole_fits<DIM, 2, T, OP>(), false>(a, *(ShmOf<DIM, 2, T, OP>*)raw, i, t.c[2].grid);
+  } else {
+    const uint32_t i = take(3);
+    single_body<DIM, T, OP>(a, i, t.c[3].grid);
+  }
+}
+template <int DIM, typename T, int OP, bool EIGHT>
+__global__ __launch_bounds__(64) void k_bricks(BrickArgs<T> a, ClassTable t) {
+  bricks_body<DIM, T, OP, EIGHT>(a, t);
+}
+// the scalar forms that fit 128 VGPRs without spills, as k_brick_o4
+template <int DIM, typename T, int OP, bool EIGHT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_bricks_o4(BrickArgs<T> a,
+                                                                                             ClassTable t) {
+  bricks_body<DIM, T, OP, EIGHT>(a, t);
 }
 
 // Block-wide deterministic sum of one double (256 threads).
@@ -1525,15 +1674,6 @@ __global__ void k_take_block(double* blk, const double* y, const uint8_t* color,
   for (int g = 0; g < nf; ++g) blk[(g * nf + field) * n + i] = y[g * n + i];
 }
 
-template <int DIM, int B, typename T, int OP>
-constexpr bool whole_fits() {
-  using TR = Traits<OP, DIM>;
-  constexpr int LPB = DIM == 3 ? B * B : B;
-  constexpr int NL = DIM == 3 ? (B + 1) * (B + 1) : (B + 1);
-  // deep bricks keep the three-layer ring (better occupancy, loads pipelined)
-  return B <= 4 && (64 / LPB) * NL * (B + 1) * (TR::NI + TR::NCF) * (int)sizeof(T) <= 12 * 1024;
-}
-
 // The uniform-mesh kernels' chunk length: node rows (2D) or layers (3D) a
 // block completes.  A chunk costs one leaf row or layer more than it owns, so
 // long chunks do less work and short ones fill the chip; `fill` blocks are
@@ -1567,56 +1707,77 @@ TileArgs<T> tile3_args(const BrickArgs<T>& b, int level) {
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 void launch_one(int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
   const dim3 g((unsigned)grid), blk(64);
-  constexpr bool W = whole_fits<DIM, B, T, OP>();
   // the scalar momentum form (viscous stiffness and density mass together)
   // needs ~140 registers: capped at four waves it spilled (88 bytes per lane
   // on table bricks), uncapped it runs three without
-  // (the pressure march on 8^3 FP64 bricks needs ~134 too: three waves)
-  if constexpr ((OP == K_PP && !(DIM == 3 && B == 8 && sizeof(T) == 8)) || OP == K_PPS || OP == K_MASS)
-    k_brick_o4<DIM, B, T, OP, W, STRUCT><<<g, blk, 0, s>>>(a);
+  if constexpr (OP == K_PP || OP == K_PPS || OP == K_MASS) k_brick_o4<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
   else if constexpr (OP == K_CH_JAC && DIM == 3 && B == 8 && STRUCT && sizeof(T) == 8)
-    k_brick_o2<DIM, B, T, OP, W, STRUCT><<<g, blk, 0, s>>>(a);
-  else k_brick<DIM, B, T, OP, W, STRUCT><<<g, blk, 0, s>>>(a);
+    k_brick_o2<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
+  else k_brick<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
 }
-template <int DIM, typename T, int OP, bool STRUCT>
-void launch_b(int B, int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
+
+// uniform 3D meshes: one brick class, node numbers computed
+template <typename T, int OP>
+void launch_structured(int B, int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
   switch (B) {
-    case 8: launch_one<DIM, 8, T, OP, STRUCT>(grid, s, a); break;
-    case 4: launch_one<DIM, 4, T, OP, STRUCT>(grid, s, a); break;
-    case 2: launch_one<DIM, 2, T, OP, STRUCT>(grid, s, a); break;
-    default: launch_one<DIM, 1, T, OP, STRUCT>(grid, s, a); break;
+    case 8: launch_one<3, 8, T, OP, true>(grid, s, a); break;
+    case 4: launch_one<3, 4, T, OP, true>(grid, s, a); break;
+    case 2: launch_one<3, 2, T, OP, true>(grid, s, a); break;
+    default: launch_one<3, 1, T, OP, true>(grid, s, a); break;
   }
+}
+
+int64_t class_blocks(const DevBrickClass& bc, int dim) {
+  const int bpb = 64 / (dim == 3 ? bc.B * bc.B : bc.B);
+  return (bc.count + bpb - 1) / bpb;
 }
 
 template <int DIM, typename T, int OP>
 int launch_bricks(const DevMesh& dm, BrickArgs<T> a, hipStream_t s, int& part_off) {
+  // the forms of several fields keep their 8^3 bricks in a launch of their
+  // own: the small bricks' LDS (16 bricks of 2^3 in a wave) would take their
+  // waves
+  constexpr bool EIGHT = OP == K_PP || OP == K_PPS || OP == K_VPS || OP == K_MASS;
+  ClassTable t{};
+  uint32_t end = 0;
+  double* part = a.partials ? a.partials + part_off : nullptr;
   for (int k = 0; k < kBrickClasses; ++k) {
     const DevBrickClass& bc = dm.cls[k];
-    if (bc.count == 0) continue;
+    const int64_t grid = bc.count ? class_blocks(bc, DIM) : 0;
     a.table = bc.table;
     a.abase = bc.abase;
     a.level = bc.level;
-    a.rank = bc.rank;
     a.count = bc.count;
     a.slot_base = bc.slot_base;
     a.nbnd = bc.nbnd;
-    double* part = a.partials;
-    const int lpb = DIM == 3 ? bc.B * bc.B : bc.B;
-    const int bpb = 64 / lpb;
-    const int64_t grid = (bc.count + bpb - 1) / bpb;
-    if (part) a.partials = part + part_off;
-    if (dm.structured) {
+    if (dm.structured || (!EIGHT && bc.B == 8)) {
+      if (!grid) continue;
       a.anchor = bc.anchor;
-      if constexpr (DIM == 3 && !(OP == K_PP && sizeof(T) == 8)) launch_b<DIM, T, OP, true>(bc.B, grid, s, a);
-    } else {
-      launch_b<DIM, T, OP, false>(bc.B, grid, s, a);
-    }
-    CHNS_HIP(hipGetLastError());
-    if (part) {
-      part_off += (int)grid;
       a.partials = part;
+      if (!dm.structured) launch_one<DIM, 8, T, OP, false>(grid, s, a);
+      else if constexpr (DIM == 3 && !(OP == K_PP && sizeof(T) == 8)) launch_structured<T, OP>(bc.B, grid, s, a);
+      CHNS_HIP(hipGetLastError());
+      if (part) {
+        part += grid;
+        part_off += (int)grid;
+      }
+      continue;
     }
+    const int at = bc.B == 8 ? 0 : bc.B == 4 ? 1 : bc.B == 2 ? 2 : 3;
+    const uint32_t g = (uint32_t)((grid + 7) / 8 * 8);
+    t.c[at] = {bc.table, bc.abase, bc.level, bc.count, bc.slot_base, bc.nbnd, 0, g};
   }
+  for (int k = 0; k < kBrickClasses; ++k) {
+    t.c[k].first = end;
+    end += t.c[k].grid;
+  }
+  if (!end) return CHNS_OK;
+  a.partials = part;
+  const dim3 g(end), blk(64);
+  if constexpr ((OP == K_PP && sizeof(T) == 4) || OP == K_PPS || OP == K_MASS) k_bricks_o4<DIM, T, OP, EIGHT><<<g, blk, 0, s>>>(a, t);
+  else k_bricks<DIM, T, OP, EIGHT><<<g, blk, 0, s>>>(a, t);
+  CHNS_HIP(hipGetLastError());
+  if (part) part_off += (int)end;
   return CHNS_OK;
 }
 
