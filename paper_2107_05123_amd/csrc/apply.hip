@@ -1684,9 +1684,13 @@ int chunk_own(int64_t tiles, int side, int64_t fill, int least) {
   return (int)std::max<int64_t>(least, (tiles * (side + 1) + fill - 1) / fill);
 }
 
+int64_t tile3_columns(int side) {
+  return (int64_t)((side + kTileX - 1) / kTileX) * ((side + kTileY - 1) / kTileY);
+}
+int tile3_own(int side) { return chunk_own(tile3_columns(side), side, 1536, 3); }
 // 3D pressure operator on a uniform mesh: arguments of k_pp_tile
 template <typename T>
-TileArgs<T> tile3_args(const BrickArgs<T>& b, int level) {
+TileArgs<T> tile3_args(const BrickArgs<T>& b, int level, int own) {
   TileArgs<T> t{};
   t.x = b.x;
   t.phi = b.cf[0];
@@ -1699,8 +1703,7 @@ TileArgs<T> tile3_args(const BrickArgs<T>& b, int level) {
   t.sm_w = b.sm_w;
   t.partials = b.partials;
   t.done = b.done;
-  tile_geometry(t, b.side, 1);
-  tile_geometry(t, b.side, chunk_own((int64_t)t.tx * t.ty, b.side, 1536, 3));
+  tile_geometry(t, b.side, own);
   return t;
 }
 
@@ -1732,12 +1735,27 @@ int64_t class_blocks(const DevBrickClass& bc, int dim) {
   return (bc.count + bpb - 1) / bpb;
 }
 
+// the forms of several fields keep their 8^3 bricks in a launch of their own:
+// the small bricks' LDS (16 bricks of 2^3 in a wave) would take their waves
+template <int OP>
+constexpr bool eight_merged() {
+  return OP == K_PP || OP == K_PPS || OP == K_VPS || OP == K_MASS;
+}
+// blocks that launch_bricks starts
+template <int DIM, int OP>
+int64_t brick_blocks(const DevMesh& dm) {
+  int64_t n = 0;
+  for (const DevBrickClass& bc : dm.cls) {
+    if (!bc.count) continue;
+    const int64_t g = class_blocks(bc, DIM);
+    n += dm.structured || (!eight_merged<OP>() && bc.B == 8) ? g : (g + 7) / 8 * 8;
+  }
+  return n;
+}
+
 template <int DIM, typename T, int OP>
 int launch_bricks(const DevMesh& dm, BrickArgs<T> a, hipStream_t s, int& part_off) {
-  // the forms of several fields keep their 8^3 bricks in a launch of their
-  // own: the small bricks' LDS (16 bricks of 2^3 in a wave) would take their
-  // waves
-  constexpr bool EIGHT = OP == K_PP || OP == K_PPS || OP == K_VPS || OP == K_MASS;
+  constexpr bool EIGHT = eight_merged<OP>();
   ClassTable t{};
   uint32_t end = 0;
   double* part = a.partials ? a.partials + part_off : nullptr;
@@ -1844,7 +1862,6 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   a.alpha = a.phys.alpha;
   a.beta = a.phys.beta;
   a.ratio = c.prm.rho_minus / c.prm.rho_plus;
-  a.partials = o.fuse_dot ? c.partials : nullptr;
   a.done = o.done;
   a.sm_r = (const T*)o.sm_r;
   a.sm_d = (const T*)o.sm_dinv;
@@ -1862,22 +1879,31 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   // of an octree with the same leaves: refinement around restarted FP32 solves
   // turns a change of rounding into a few iterations (327 to 338 for the
   // learned preconditioner at 128^3), and the two paths agree exactly.
-  bool whole = false;
-  if (dm.structured) {
+  constexpr bool TILE3 = DIM == 3 && OP == K_PP && sizeof(T) == 8;
+  const bool whole = dm.structured && (DIM == 2 || TILE3);
+  const int tx2 = std::max(1, (dm.side - 1 + kTile2X - 1) / kTile2X);
+  const int own = !whole ? 1 : DIM == 2 ? chunk_own(tx2, dm.side, 6144, 2) : tile3_own(dm.side);
+  const int64_t cb = whole ? 0 : combine_blocks(dm);
+  const int64_t total = !whole ? brick_blocks<DIM, OP>(dm) + cb
+                               : (DIM == 2 ? tx2 : tile3_columns(dm.side)) * (int64_t)((dm.side + own) / own);
+  const bool fold = o.fuse_dot && o.fold && total <= kFoldPartials;
+  if (o.fold) *o.fold = fold ? (int)total : 0;
+  if (o.fuse_dot && total > kMaxPartials) {
+    set_error("mesh needs more reduction partials than allocated");
+    return CHNS_EINVAL;
+  }
+  double* const parts = o.fuse_dot ? c.partials + (fold ? o.fold_at : 0) : nullptr;
+  a.partials = parts;
+  if (whole) {
+    c.prof_begin(tag, s, &ev);
     if constexpr (DIM == 2) {
-      const int tx = std::max(1, (dm.side - 1 + kTile2X - 1) / kTile2X);
-      const int own = chunk_own(tx, dm.side, 6144, 2);
-      part_off = tx * ((dm.side + own) / own);
-      c.prof_begin(tag, s, &ev);
-      k_tile2<T, OP><<<dim3((unsigned)part_off), dim3(64), 0, s>>>(a, tx, own);
-      whole = true;
-    } else if constexpr (OP == K_PP && sizeof(T) == 8) {
-      const TileArgs<T> t = tile3_args<T>(a, dm.max_level);
-      part_off = t.blocks();
-      c.prof_begin(tag, s, &ev);
-      if (t.sm_r) k_pp_tile<T, true><<<dim3((unsigned)part_off), dim3(256), 0, s>>>(t);
-      else k_pp_tile<T, false><<<dim3((unsigned)part_off), dim3(256), 0, s>>>(t);
-      whole = true;
+      k_tile2<T, OP><<<dim3((unsigned)total), dim3(64), 0, s>>>(a, tx2, own);
+      part_off = (int)total;
+    } else if constexpr (TILE3) {
+      const TileArgs<T> t = tile3_args<T>(a, dm.max_level, own);
+      if (t.sm_r) k_pp_tile<T, true><<<dim3((unsigned)total), dim3(256), 0, s>>>(t);
+      else k_pp_tile<T, false><<<dim3((unsigned)total), dim3(256), 0, s>>>(t);
+      part_off = (int)total;
     }
   }
   if (whole) {
@@ -1888,24 +1914,16 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
     if (rc) return rc;
   }
   c.prof_end(tag, s, ev);
-  const int64_t cb = whole ? 0 : combine_blocks(dm);
-  const int total = part_off + (int)cb;
-  if (o.fuse_dot && total > kMaxPartials) {
-    set_error("mesh needs more reduction partials than allocated");
-    return CHNS_EINVAL;
-  }
-  if (!whole && (cb > 0 || o.fuse_dot)) {
-    const unsigned g = (unsigned)(cb > 0 ? cb : 1);
+  if (cb > 0) {
     c.prof_begin("combine", s, &ev);
-    k_combine<T, TR::NO, TR::WALL><<<dim3(g), dim3(256), 0, s>>>(
+    k_combine<T, TR::NO, TR::WALL><<<dim3((unsigned)cb), dim3(256), 0, s>>>(
         dm.comb_node, dm.comb_ptr, dm.comb_ent, dm.n_comb, (const T*)L.slots, dm.n_slots, y, x, dm.n, dm.wall,
-        o.fuse_dot ? c.partials + part_off : nullptr, o.done, (const T*)o.sm_r, (const T*)o.sm_dinv,
-        (T)o.sm_w);
+        parts ? parts + part_off : nullptr, o.done, (const T*)o.sm_r, (const T*)o.sm_dinv, (T)o.sm_w);
     CHNS_HIP(hipGetLastError());
     c.prof_end("combine", s, ev);
   }
-  if (o.fuse_dot) {
-    k_sum_partials<<<1, 1024, 0, s>>>(c.partials, total, &c.sc->pq, o.done);
+  if (o.fuse_dot && !fold) {
+    k_sum_partials<<<1, 1024, 0, s>>>(parts, (int)total, &c.sc->pq, o.done);
     CHNS_HIP(hipGetLastError());
   }
   return CHNS_OK;

@@ -224,6 +224,7 @@ struct Ctx {
 constexpr size_t kScratchBytes = size_t(32) << 20;
 constexpr int kMaxDevices = 64;
 constexpr int kMaxPartials = 1 << 20;  // per-block reduction partials (bricks + combine blocks of the largest meshes)
+constexpr int kFoldPartials = 2048;    // partials a consumer sums itself in each of its blocks
 constexpr int kMaxCoefFields = 16;  // coefficient fields one element form may read
 
 // A mesh level as seen by the apply kernels: the fine level of a context or
@@ -239,6 +240,11 @@ struct LevelView {
 struct ApplyOut {
   // optional fused reduction: sum_i x_i * y_i over written nodes into sc->pq
   bool fuse_dot = false;
+  // with fuse_dot: where few enough partials arise (kFoldPartials), leave them
+  // at c.partials + fold_at, their number in *fold, for the next kernel to
+  // sum; otherwise the sum goes to sc->pq and *fold is 0
+  int* fold = nullptr;
+  int fold_at = 0;
   const int* done = nullptr;  // skip all work when *done != 0
   // pressure operator only: a damped-Jacobi sweep instead of the product,
   // y = x + w dinv (r - A x) (y must not alias x); vectors of the apply's

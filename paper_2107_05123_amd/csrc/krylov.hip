@@ -33,6 +33,8 @@ __device__ __forceinline__ double wsum(double v) {
 // totals are formed by a one-block finalisation kernel launched next on the
 // same stream (kernel boundaries order the writes; no per-block fences).
 constexpr int kStride = kMaxPartials / 4;
+// partials of p.Ap (the apply's) when the update kernel sums them itself
+constexpr int kPqPart = 3 * kStride;
 template <int NV>
 __device__ void block_partials(double (&v)[NV], double* partials) {
   __shared__ double sh[NV][4];
@@ -49,7 +51,26 @@ __device__ void block_partials(double (&v)[NV], double* partials) {
   }
 }
 
-enum FinMode { FIN_STORE = 0, FIN_CG_INIT = 1, FIN_CG_UPDATE = 2, FIN_FCG_UPDATE = 3, FIN_FCG_CONT = 4 };
+// Sum of n partials by a 256-thread block in a fixed order, the same total in
+// every thread and in every block that forms it.
+__device__ double fold_sum(const double* part, int n, double* sh) {
+  double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
+  int b = threadIdx.x;
+  for (; b + 3 * kThreads < n; b += 4 * kThreads) {
+    v0 += part[b];
+    v1 += part[b + kThreads];
+    v2 += part[b + 2 * kThreads];
+    v3 += part[b + 3 * kThreads];
+  }
+  for (; b < n; b += kThreads) v0 += part[b];
+  const double v = wsum((v0 + v1) + (v2 + v3));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+enum FinMode { FIN_STORE = 0, FIN_CG_INIT = 1, FIN_FCG_CONT = 2 };
 
 // Fixed-order totals of nv partial arrays, then the scalar update of `mode`.
 // 1024 threads, each with four independent running sums, so the few thousand
@@ -86,7 +107,7 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(const double* partials
   if (threadIdx.x != 0) return;
   if (mode == FIN_STORE) {
     *out = tot[0];
-  } else if (mode == FIN_CG_INIT || mode == FIN_FCG_CONT) {
+  } else {
     sc->rz = tot[0];
     sc->rr = tot[1];
     sc->it = 0;
@@ -96,21 +117,6 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(const double* partials
     // converged, or breakdown: a non-finite residual or r.z <= 0 (an
     // indefinite or vanishing preconditioner output) ends the solve at x_0
     sc->done = (tot[1] <= sc->tol2 || !(tot[1] == tot[1]) || !(tot[0] > 0.0)) ? 1 : 0;
-  } else {
-    // CG: beta = (r_new.z_new) / (r_old.z_old); flexible CG (Polak-Ribiere
-    // form): beta = z_new.(r_new - r_old) / (r_old.z_old)
-    sc->rz_old = sc->rz;
-    sc->rz = tot[0];
-    sc->rr = tot[1];
-    sc->beta = (mode == FIN_FCG_UPDATE ? tot[0] - tot[2] : tot[0]) / sc->rz_old;
-    sc->it = sc->it + 1;
-    // the update kernel skipped this step when p.Ap <= 0 (see k_cg_update);
-    // r.z <= 0 would make the next step length meaningless: both end the solve
-    // at the last iterate, as does a non-finite residual
-    sc->done = (tot[1] <= sc->tol2 || sc->it >= sc->max_it || !(tot[1] == tot[1]) || !(sc->pq > 0.0) ||
-                !(tot[0] > 0.0))
-                   ? 1
-                   : 0;
   }
   if (flag_host && mode != FIN_STORE) {
     // vector stores with system scope into pinned host memory; visible to
@@ -120,9 +126,11 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(const double* partials
   }
 }
 
+// vector kernels: four blocks on each CU stream at full rate, and every block
+// of the next kernel can still read all their partials
 inline unsigned grid_for(int64_t n) {
   int64_t g = (n + kThreads - 1) / kThreads;
-  if (g > 2048) g = 2048;
+  if (g > 1024) g = 1024;
   if (g < 1) g = 1;
   return (unsigned)g;
 }
@@ -201,15 +209,28 @@ __global__ __launch_bounds__(kThreads) void k_cg_init(const T* b, const T* q, T*
   block_partials<2>(v, partials);
 }
 
+// Step length of a CG iteration, p.Ap summed by every block from the apply's
+// npq partials (which lie behind the update's own); the first block leaves
+// what k_cg_next needs: p.Ap, the old r.z and the iteration count, none of
+// which another block of this kernel reads.  npq = 0: sc->pq holds the sum.
+// p.Ap <= 0 (breakdown of a non-SPD preconditioner, or p = 0): no step.
+__device__ double cg_alpha(DevScalars* sc, const double* partials, int npq) {
+  __shared__ double sh[4];
+  const double rz = sc->rz;
+  const double pq = npq > 0 ? fold_sum(partials + kPqPart, npq, sh) : sc->pq;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (npq > 0) sc->pq = pq;
+    sc->rz_old = rz;
+    sc->it = sc->it + 1;
+  }
+  return pq > 0.0 ? rz / pq : 0.0;
+}
 // alpha = rz/pq; x += alpha p; r -= alpha q; z = dinv r; new rz, rr; beta
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_cg_update(T* x, T* r, T* z, const T* p, const T* q, const T* dinv,
-                                                        int64_t n, DevScalars* sc, double* partials,
-                                                        unsigned* counter) {
+                                                        int64_t n, DevScalars* sc, double* partials, int npq) {
   if (sc->done) return;
-  // p.Ap <= 0 (breakdown of a non-SPD preconditioner, or p = 0): no step
-  const double alpha = sc->pq > 0.0 ? sc->rz / sc->pq : 0.0;
-  const T a = (T)alpha;
+  const T a = (T)cg_alpha(sc, partials, npq);
   double v[2] = {0.0, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
     T xi = x[i] + a * p[i];
@@ -224,12 +245,53 @@ __global__ __launch_bounds__(kThreads) void k_cg_update(T* x, T* r, T* z, const 
   block_partials<2>(v, partials);
 }
 
+// End of a CG iteration: every block forms the totals of the update's partials
+// and from them beta and whether the solve is over (the same in all of them),
+// then p = z + beta p; the first block stores the scalars and the host's flag.
+// CG: beta = (r_new.z_new) / (r_old.z_old); flexible CG (Polak-Ribiere form):
+// beta = z_new.(r_new - r_old) / (r_old.z_old).
+//
+// The two one-block reduction kernels this replaces (the sum of p.Ap and the
+// finalisation) cost 4.4 + 5.2 us of a 43 us iteration at 64^3 and more than
+// the vector work below that; the partials are few enough (at most 1,024 and
+// 2,048) for each block to read them out of the L2.
 template <typename T>
-__global__ void k_cg_p(T* p, const T* z, int64_t n, const DevScalars* sc, int check_done) {
-  if (check_done && sc->done) return;
-  const T beta = (T)sc->beta;
+__global__ __launch_bounds__(kThreads) void k_cg_next(T* p, const T* z, int64_t n, DevScalars* sc,
+                                                      const double* partials, int nparts, int flexible,
+                                                      int* flag_host) {
+  __shared__ double sh[4];
+  __shared__ int over;
+  // read once per block: the first block may set the flag meanwhile (a block
+  // that sees it has nothing left to do either)
+  if (threadIdx.x == 0) over = sc->done;
+  __syncthreads();
+  if (over) return;
+  const double rz_old = sc->rz_old, pq = sc->pq, tol2 = sc->tol2;
+  const int it = sc->it, max_it = sc->max_it;
+  const double rz = fold_sum(partials, nparts, sh);
+  const double rr = fold_sum(partials + kStride, nparts, sh);
+  const double ro = flexible ? fold_sum(partials + 2 * kStride, nparts, sh) : 0.0;
+  const double beta = (flexible ? rz - ro : rz) / rz_old;
+  // the update kernel skipped this step when p.Ap <= 0; r.z <= 0 would make
+  // the next step length meaningless: both end the solve at the last iterate,
+  // as does a non-finite residual
+  const bool done = rr <= tol2 || it >= max_it || !(rr == rr) || !(pq > 0.0) || !(rz > 0.0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sc->rz = rz;
+    sc->rr = rr;
+    sc->beta = beta;
+    if (flag_host) {
+      // vector stores with system scope into pinned host memory; visible to
+      // the host once an event recorded after this kernel has completed
+      __hip_atomic_store(&flag_host[1], it, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(&flag_host[0], done ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (done) sc->done = 1;
+  }
+  if (done) return;
+  const T b = (T)beta;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
-    p[i] = z[i] + beta * p[i];
+    p[i] = z[i] + b * p[i];
 }
 
 // continued search direction after a residual replacement, in the units of
@@ -262,9 +324,9 @@ __global__ __launch_bounds__(kThreads) void k_cg_init_nopc(const T* b, const T* 
 // alpha = rz/pq; x += alpha p; (r_old = r); r -= alpha q; partial r.r (slot 1)
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_cg_update_nopc(T* x, T* r, T* r_old, const T* p, const T* q, int64_t n,
-                                                             const DevScalars* sc, double* partials) {
+                                                             DevScalars* sc, double* partials, int npq) {
   if (sc->done) return;
-  const T a = (T)(sc->pq > 0.0 ? sc->rz / sc->pq : 0.0);
+  const T a = (T)cg_alpha(sc, partials, npq);
   double v[2] = {0.0, 0.0};
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
     const T ri = r[i];
@@ -460,7 +522,11 @@ int pcg(Ctx& c, int op, const T* b, T* x, int pc, const T* dinv, bool flexible, 
   T* r_old = flexible ? w[6] : nullptr;
   const bool fused_pc = pc == PCK_NONE || pc == PCK_JACOBI;
   const unsigned g = grid_for(n);
-  Poller poll(c, s, std::max(1, depth));
+  // cheap iterations go four to a graph: a graph launch costs the device
+  // several microseconds between iterations of three short kernels, and
+  // iterations past the end are no-ops (the kernels test the done flag)
+  const int batch = fused_pc && graphs && !c.prof ? 4 : 1;
+  Poller poll(c, s, std::max(1, depth / batch));
   int rc = poll.init();
   if (rc) return rc;
   k_init_scalars<<<1, 1, 0, s>>>(c.sc, tol2, max_it);
@@ -489,19 +555,20 @@ int pcg(Ctx& c, int op, const T* b, T* x, int pc, const T* dinv, bool flexible, 
   fused.fuse_dot = true;
   fused.done = &c.sc->done;
   auto iteration = [&](hipStream_t st, int pck) -> int {
-    int e;
+    int e, npq = 0;
+    fused.fold = &npq;
+    fused.fold_at = kPqPart;
     if ((e = launch_apply(c, op, prec, p, q, st, fused))) return e;
     if (fused_pc) {
       k_cg_update<T><<<g, kThreads, 0, st>>>(x, r, z, p, q, pc == PCK_JACOBI ? dinv : nullptr, n, c.sc,
-                                             c.partials, c.counter);
-      if ((e = fin(c, st, g, 2, FIN_CG_UPDATE, nullptr, 1))) return e;
+                                             c.partials, npq);
     } else {
-      k_cg_update_nopc<T><<<g, kThreads, 0, st>>>(x, r, r_old, p, q, n, c.sc, c.partials);
+      k_cg_update_nopc<T><<<g, kThreads, 0, st>>>(x, r, r_old, p, q, n, c.sc, c.partials, npq);
       if ((e = apply_pc<T>(c, pck, r, z, st, dinv, n))) return e;
       k_dot_rz<T><<<g, kThreads, 0, st>>>(r, z, r_old, n, c.sc, c.partials, 1);
-      if ((e = fin(c, st, g, flexible ? 3 : 2, flexible ? FIN_FCG_UPDATE : FIN_CG_UPDATE, nullptr, 1))) return e;
     }
-    k_cg_p<T><<<g, kThreads, 0, st>>>(p, z, n, c.sc, 1);
+    k_cg_next<T><<<g, kThreads, 0, st>>>(p, z, n, c.sc, c.partials, (int)g, flexible && !fused_pc ? 1 : 0,
+                                         c.flag_host);
     CHNS_HIP(hipGetLastError());
     return CHNS_OK;
   };
@@ -519,7 +586,8 @@ int pcg(Ctx& c, int op, const T* b, T* x, int pc, const T* dinv, bool flexible, 
     hipGraph_t graph = nullptr;
     hipGraphExec_t ex = nullptr;
     CHNS_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
-    int e = iteration(s, pck);
+    int e = 0;
+    for (int k = 0; k < batch && !e; ++k) e = iteration(s, pck);
     hipError_t ce = hipStreamEndCapture(s, &graph);
     if (e) return e;
     if (ce != hipSuccess) return hip_fail(ce, "hipStreamEndCapture");
@@ -535,20 +603,18 @@ int pcg(Ctx& c, int op, const T* b, T* x, int pc, const T* dinv, bool flexible, 
   if ((rc = get_graph(pc, &exec))) return rc;
   if (sched && (rc = get_graph(PCK_JACOBI_FLEX, &exec_j))) return rc;
   bool done = false;
-  int it = 0;
-  while (true) {
-    const bool jac = sched && (sched_offset + it + 1) % every != 0;
+  for (int k = 0;; ++k) {  // batches of iterations
+    const bool jac = sched && (sched_offset + k + 1) % every != 0;
     hipGraphExec_t ex = jac ? exec_j : exec;
     if (ex) {
       CHNS_HIP(hipGraphLaunch(ex, s));
     } else if ((rc = iteration(s, jac ? PCK_JACOBI_FLEX : pc))) {
       return rc;
     }
-    if ((rc = poll.post(it))) return rc;
-    ++it;
-    if (it >= max_it) break;
-    if (it >= depth) {
-      if ((rc = poll.wait(it - depth, &done))) return rc;
+    if ((rc = poll.post(k))) return rc;
+    if ((int64_t)(k + 1) * batch >= max_it) break;
+    if (k + 1 >= poll.depth) {
+      if ((rc = poll.wait(k + 1 - poll.depth, &done))) return rc;
       if (done) break;
     }
   }
