@@ -96,19 +96,21 @@ __host__ __device__ constexpr int insert0(int r, int d) { return (r & ((1 << d) 
 // Pressure Poisson: y_a = sum_q detJ (2/h)^2 c_q gradN_a . grad x,
 // c_q = 1/rho(clamp(phi_q)) (Def. 2, VMS pressure Poisson; pull back remark).
 template <int DIM, typename T, bool RCP = true>
-__device__ __forceinline__ void elem_pp(const T* x, const T* ph, T A, T Bc, T* y) {
-  constexpr int NC = 1 << DIM, H = NC / 2;
-  T q[NC];
+__device__ __forceinline__ void elem_pp_coef(const T* ph, T A, T Bc, T* c) {
+  constexpr int NC = 1 << DIM;
 #pragma unroll
-  for (int i = 0; i < NC; ++i) q[i] = ph[i];
-  all_stages<DIM>(q);
-  T c[NC];
+  for (int i = 0; i < NC; ++i) c[i] = ph[i];
+  all_stages<DIM>(c);
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
     // coefficient 1 / (A phi + B) (pressure) or A phi + B (viscosity)
-    const T lin = fma_t(A, clamp_t(q[i], T(NC)), Bc);
+    const T lin = fma_t(A, clamp_t(c[i], T(NC)), Bc);
     c[i] = RCP ? rcp_t(lin) : lin;
   }
+}
+template <int DIM, typename T>
+__device__ __forceinline__ void elem_pp_apply(const T* x, const T* c, T* y) {
+  constexpr int NC = 1 << DIM, H = NC / 2;
 #pragma unroll
   for (int i = 0; i < NC; ++i) y[i] = T(0);
 #pragma unroll
@@ -135,6 +137,13 @@ __device__ __forceinline__ void elem_pp(const T* x, const T* ph, T A, T Bc, T* y
       y[lo] -= g[r];
     }
   }
+}
+
+template <int DIM, typename T, bool RCP = true>
+__device__ __forceinline__ void elem_pp(const T* x, const T* ph, T A, T Bc, T* y) {
+  T c[1 << DIM];
+  elem_pp_coef<DIM, T, RCP>(ph, A, Bc, c);
+  elem_pp_apply<DIM, T>(x, c, y);
 }
 
 // Mass: y_a = sum_q detJ r_q N_a (N . x), r_q = rho(clamp(phi_q)) or 1.
@@ -169,7 +178,7 @@ __device__ __forceinline__ void elem_mass_apply(const T* x, const T* r, T* y) {
 // 1 identity rows on the walls (y = x), 2 zero rows on the walls.
 enum OpKind {
   K_PP = 0, K_MASS = 1, K_MASS_RHO = 2, K_CH_RES = 3, K_CH_JAC = 4, K_VP = 5, K_VP_RHS = 6, K_PP_RHS = 7,
-  K_VU_RHS = 8, K_ENERGY = 9, K_PPS = 10, K_VPS = 11
+  K_VU_RHS = 8, K_ENERGY = 9, K_PPS = 10, K_VPS = 11, K_DIAG = 12
 };
 template <int OP, int DIM>
 struct Traits;
@@ -191,6 +200,7 @@ CHNS_TRAITS(K_VU_RHS, 0, 4 * DIM + 4, DIM, false, 2)
 CHNS_TRAITS(K_ENERGY, 0, 2 + DIM, 1, false, 0)
 CHNS_TRAITS(K_PPS, 1, 1, 1, false, 0)  // pressure operator + shift * mass
 CHNS_TRAITS(K_VPS, 1, 1, 1, false, 0)  // scalar momentum: K_{eta/(2 Re)} + M_{rho/dt}
+CHNS_TRAITS(K_DIAG, 1, 1, 1, false, 0)  // diagonal of the scalar operators (the input is the node entry itself)
 #undef CHNS_TRAITS
 
 constexpr int kMaxCoef = kMaxCoefFields;
@@ -221,6 +231,7 @@ struct BrickArgs {
   const T* sm_d;
   T sm_w;
   double shift;  // K_PPS: mass shift
+  int diag_of;   // K_DIAG: the operator's form
   // structured (uniform, lexicographically numbered) meshes: node indices are
   // computed from the brick anchor instead of read from the table
   const int32_t* anchor;  // 3 per brick, integer node coordinates
@@ -783,6 +794,99 @@ __device__ __forceinline__ OpConst<T> op_const(const BrickArgs<T>& a, int lev) {
   return o;
 }
 
+// One leaf's share of the exact diagonal of P^T K P for a scalar operator
+// (a.diag_of: pressure with or without a mass shift, scalar momentum, mass,
+// density mass): sum over its corner pairs (a, b) of P_ai P_bi K_ab for every
+// independent node i.  The share goes through the corners' slots, which the
+// combine adds with the squared constraint weights (1, 1/4, 1/16), so corner a
+// takes K_aa, and the pairs with a hanging corner are written as follows.
+//   * a independent and a parent of b (weight w): node a takes 2 w K_ab;
+//   * both hanging with one common parent: it is a corner of the leaf (on a
+//     2:1-balanced octree the parents outside the leaf belong to whole edges
+//     or faces) and takes 2 w_a w_b K_ab;
+//   * both hanging with two common parents: those are the ends of a split edge
+//     of the leaf, whose midpoint m is a hanging corner with weights 1/2, so m
+//     takes 2 w_a w_b K_ab / (1/2)^2.
+// e: the corners' node entries (negative: hanging record).
+template <int DIM, typename T>
+__device__ __forceinline__ void leaf_diag(const BrickArgs<T>& a, int lev, const T* e, const T* ph, T* y) {
+  constexpr int NC = 1 << DIM;
+  const bool pp = a.diag_of == K_PP || a.diag_of == K_PPS, vps = a.diag_of == K_VPS;
+  T c[NC], r[NC];
+  if (pp) {
+    const OpConst<T> o = op_const<DIM, T, K_PPS>(a, lev);
+    elem_pp_coef<DIM, T, true>(ph, o.A, o.Bc, c);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) r[i] = a.diag_of == K_PPS ? o.Ms : T(0);
+  } else if (vps) {
+    const OpConst<T> o = op_const<DIM, T, K_VPS>(a, lev);
+    elem_pp_coef<DIM, T, false>(ph, o.A, o.Bc, c);
+    elem_mass_coef<DIM, T, true>(ph, o.Am, o.Bm, r);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NC; ++i) c[i] = T(0);
+    if (a.diag_of == K_MASS_RHO) {
+      const OpConst<T> o = op_const<DIM, T, K_MASS_RHO>(a, lev);
+      elem_mass_coef<DIM, T, true>(ph, o.A, o.Bc, r);
+    } else {
+      const T m = op_const<DIM, T, K_MASS>(a, lev).Bc;
+#pragma unroll
+      for (int i = 0; i < NC; ++i) r[i] = m;
+    }
+  }
+  int32_t par[NC][4];
+  bool hang = false;
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int32_t n = (int32_t)e[i];
+    y[i] = T(0);
+    par[i][0] = n;
+    par[i][1] = par[i][2] = par[i][3] = -1;
+    if (n < 0) {
+      hang = true;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) par[i][k] = a.hang[4 * (int64_t)(-n - 1) + k];
+    }
+  }
+  auto weight = [&](int i) { return par[i][1] < 0 ? T(1) : par[i][2] < 0 ? T(0.5) : T(0.25); };
+#pragma unroll
+  for (int b = 0; b < NC; ++b) {
+    // column b of the leaf matrix
+    T x[NC], k[NC], km[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) x[i] = T(i == b ? 1 : 0);
+    elem_pp_apply<DIM, T>(x, c, k);
+    elem_mass_apply<DIM, T>(x, r, km);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) k[i] += km[i];
+    y[b] += k[b];
+    if (!hang) continue;
+#pragma unroll
+    for (int i = 0; i < b; ++i) {
+      if (par[i][1] < 0 && par[b][1] < 0) continue;  // two independent corners
+      const T w = T(2) * weight(i) * weight(b) * k[i];
+      int32_t s0 = -1, s1 = -1;  // common parents
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (par[i][p] >= 0 && par[i][p] == par[b][q]) {
+            s1 = s0;
+            s0 = par[i][p];
+          }
+      if (s0 < 0) continue;
+#pragma unroll
+      for (int m = 0; m < NC; ++m) {
+        const bool one = s1 < 0 && par[m][1] < 0 && par[m][0] == s0;
+        const bool two = s1 >= 0 && par[m][1] >= 0 && par[m][2] < 0 &&
+                         ((par[m][0] == s0 && par[m][1] == s1) || (par[m][0] == s1 && par[m][1] == s0));
+        if (one) y[m] += w;
+        if (two) y[m] += T(4) * w;
+      }
+    }
+  }
+}
+
 // One leaf of the form OP: corner values xc (inputs) and cc (coefficients),
 // or the accessor cv(f, a) for the heavy forms, to corner results ye.  The
 // momentum form instead hands each component's results to out(f, y) in turn.
@@ -794,7 +898,9 @@ __device__ __forceinline__ void leaf_form(const BrickArgs<T>& a, const OpConst<T
   constexpr int NI = TR::NI, NC = 1 << DIM;
   // CHNS forms: physical gradient scale 2/h and det J = (h/2)^d
   const double gs = ldexp(1.0, lev + 1), wdet = ldexp(1.0, -(lev + 1) * DIM);
-  if constexpr (OP == K_CH_JAC) {
+  if constexpr (OP == K_DIAG) {
+    leaf_diag<DIM, T>(a, lev, xc[0], cc[0], ye[0]);
+  } else if constexpr (OP == K_CH_JAC) {
     el_chj<DIM, T>(cv, a.phys, lev, ye);
   } else if constexpr (OP == K_VP) {
     el_vp<DIM, T>(cv, a.phys, lev, out);
@@ -844,7 +950,9 @@ __device__ __forceinline__ void table_first(const BrickArgs<T>& a, int32_t e, T*
   const int32_t i = e >= 0 ? e : 0;
 #pragma unroll
   for (int f = 0; f < TR::NI + TR::NCF; ++f)
-    v[f] = f < TR::NI ? fetch<T, TR::MASK>(a.x + f * a.n, a.wall, i) : a.cf[f - TR::NI][i];
+    v[f] = OP == K_DIAG && f == 0 ? T(e)
+           : f < TR::NI           ? fetch<T, TR::MASK>(a.x + f * a.n, a.wall, i)
+                                  : a.cf[f - TR::NI][i];
 }
 template <int DIM, typename T, int OP>
 __device__ __forceinline__ void table_parents(const BrickArgs<T>& a, int32_t e, T* v) {
@@ -854,7 +962,7 @@ __device__ __forceinline__ void table_parents(const BrickArgs<T>& a, int32_t e, 
   const bool four = p2 >= 0;
   const int32_t q2 = four ? p2 : p0, q3 = four ? p3 : p1;
 #pragma unroll
-  for (int f = 0; f < TR::NI + TR::NCF; ++f) {
+  for (int f = OP == K_DIAG ? 1 : 0; f < TR::NI + TR::NCF; ++f) {
     T v0, v1, v2, v3;
     if (f < TR::NI) {
       const T* src = a.x + f * a.n;
@@ -1552,7 +1660,7 @@ __device__ double block_sum256(double v, double* sh) {
   return r;
 }
 
-template <typename T, int NO, int WALL>
+template <typename T, int NO, int WALL, bool SQ>
 __global__ __launch_bounds__(256) void k_combine(const int32_t* __restrict__ node, const int32_t* __restrict__ ptr,
                                                  const uint32_t* __restrict__ ent, int64_t nrows,
                                                  const T* __restrict__ slots, int64_t n_slots, T* __restrict__ y,
@@ -1586,7 +1694,8 @@ __global__ __launch_bounds__(256) void k_combine(const int32_t* __restrict__ nod
         for (int j = 0; j < CH; ++j) {
           if (kb + j < k1) {
             const uint32_t code = e[j] >> 30;
-            v[f] += code == 0 ? sv[j] : (code == 1 ? sv[j] * T(0.5) : sv[j] * T(0.25));
+            // SQ: squared weights (diagonals)
+            v[f] += code == 0 ? sv[j] : (code == 1 ? sv[j] * T(SQ ? 0.25 : 0.5) : sv[j] * T(SQ ? 0.0625 : 0.25));
           }
         }
       }
@@ -1665,6 +1774,19 @@ __global__ void k_take_diag(T* d, const T* y, const uint8_t* color, int c, int64
     d[f * n + i] = invert ? (v != T(0) ? T(1) / v : T(1)) : v;
   }
 }
+// one-pass diagonal: the same for every field, 1 on the walls of an operator
+// with identity wall rows (wall != null), inverted on request
+__global__ void k_diag_finish(double* d, int64_t n, int nf, const uint8_t* wall, int invert) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  double v = wall && wall[i] ? 1.0 : d[i];
+  if (invert) v = v != 0.0 ? 1.0 / v : 1.0;
+  for (int f = 0; f < nf; ++f) d[f * n + i] = v;
+}
+__global__ void k_narrow(const double* a, float* b, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    b[i] = (float)a[i];
+}
 // column `field` of the nf x nf node blocks: blk[(g * nf + field) * n + i] = y_g,i
 __global__ void k_take_block(double* blk, const double* y, const uint8_t* color, int c, int64_t n, int nf,
                              int field) {
@@ -1739,7 +1861,7 @@ int64_t class_blocks(const DevBrickClass& bc, int dim) {
 // the small bricks' LDS (16 bricks of 2^3 in a wave) would take their waves
 template <int OP>
 constexpr bool eight_merged() {
-  return OP == K_PP || OP == K_PPS || OP == K_VPS || OP == K_MASS;
+  return OP == K_PP || OP == K_PPS || OP == K_VPS || OP == K_MASS || OP == K_DIAG;
 }
 // blocks that launch_bricks starts
 template <int DIM, int OP>
@@ -1772,8 +1894,11 @@ int launch_bricks(const DevMesh& dm, BrickArgs<T> a, hipStream_t s, int& part_of
       if (!grid) continue;
       a.anchor = bc.anchor;
       a.partials = part;
-      if (!dm.structured) launch_one<DIM, 8, T, OP, false>(grid, s, a);
-      else if constexpr (DIM == 3 && !(OP == K_PP && sizeof(T) == 8)) launch_structured<T, OP>(bc.B, grid, s, a);
+      if constexpr (!EIGHT) {
+        if (!dm.structured) launch_one<DIM, 8, T, OP, false>(grid, s, a);
+      }
+      if constexpr (DIM == 3 && !(OP == K_PP && sizeof(T) == 8) && OP != K_DIAG)
+        if (dm.structured) launch_structured<T, OP>(bc.B, grid, s, a);
       CHNS_HIP(hipGetLastError());
       if (part) {
         part += grid;
@@ -1820,7 +1945,7 @@ Phys phys_of(const chns_params& p) {
 }
 
 const char* op_tag(int op, bool fp64) {
-  static const char* tags[12][2] = {{"pp_brick_fp64", "pp_brick_fp32"},
+  static const char* tags[13][2] = {{"pp_brick_fp64", "pp_brick_fp32"},
                                     {"mass_brick_fp64", "mass_brick_fp32"},
                                     {"massrho_brick_fp64", "massrho_brick_fp32"},
                                     {"chres_brick_fp64", "chres_brick_fp32"},
@@ -1831,7 +1956,8 @@ const char* op_tag(int op, bool fp64) {
                                     {"vurhs_brick_fp64", "vurhs_brick_fp32"},
                                     {"energy_brick_fp64", "energy_brick_fp32"},
                                     {"pps_brick_fp64", "pps_brick_fp32"},
-                                    {"vps_brick_fp64", "vps_brick_fp32"}};
+                                    {"vps_brick_fp64", "vps_brick_fp32"},
+                                    {"diag_brick_fp64", "diag_brick_fp32"}};
   return tags[op][fp64 ? 0 : 1];
 }
 
@@ -1867,6 +1993,7 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   a.sm_d = (const T*)o.sm_dinv;
   a.sm_w = (T)o.sm_w;
   a.shift = c.pp_shift;
+  a.diag_of = o.diag_of;
   a.sy = dm.side + 1;
   a.sz = (int64_t)(dm.side + 1) * (dm.side + 1);
   a.side = dm.side;
@@ -1880,7 +2007,7 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   // turns a change of rounding into a few iterations (327 to 338 for the
   // learned preconditioner at 128^3), and the two paths agree exactly.
   constexpr bool TILE3 = DIM == 3 && OP == K_PP && sizeof(T) == 8;
-  const bool whole = dm.structured && (DIM == 2 || TILE3);
+  const bool whole = dm.structured && (DIM == 2 || TILE3) && OP != K_DIAG;
   const int tx2 = std::max(1, (dm.side - 1 + kTile2X - 1) / kTile2X);
   const int own = !whole ? 1 : DIM == 2 ? chunk_own(tx2, dm.side, 6144, 2) : tile3_own(dm.side);
   const int64_t cb = whole ? 0 : combine_blocks(dm);
@@ -1896,7 +2023,7 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   a.partials = parts;
   if (whole) {
     c.prof_begin(tag, s, &ev);
-    if constexpr (DIM == 2) {
+    if constexpr (DIM == 2 && OP != K_DIAG) {
       k_tile2<T, OP><<<dim3((unsigned)total), dim3(64), 0, s>>>(a, tx2, own);
       part_off = (int)total;
     } else if constexpr (TILE3) {
@@ -1916,7 +2043,7 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   c.prof_end(tag, s, ev);
   if (cb > 0) {
     c.prof_begin("combine", s, &ev);
-    k_combine<T, TR::NO, TR::WALL><<<dim3((unsigned)cb), dim3(256), 0, s>>>(
+    k_combine<T, TR::NO, TR::WALL, OP == K_DIAG><<<dim3((unsigned)cb), dim3(256), 0, s>>>(
         dm.comb_node, dm.comb_ptr, dm.comb_ent, dm.n_comb, (const T*)L.slots, dm.n_slots, y, x, dm.n, dm.wall,
         parts ? parts + part_off : nullptr, o.done, (const T*)o.sm_r, (const T*)o.sm_dinv, (T)o.sm_w);
     CHNS_HIP(hipGetLastError());
@@ -2101,15 +2228,42 @@ int launch_form(Ctx& c, int form, const double* x, const double* const* cf, doub
   return CHNS_EINVAL;
 }
 
-// Exact diagonal of P^T K P by probing: colour classes never share a leaf
-// (directly or through constraint parents), so y = A 1_c has y_i = A_ii on
-// colour c.
+int launch_narrow(const double* a, float* b, int64_t n, hipStream_t s) {
+  k_narrow<<<(unsigned)std::min<int64_t>((n + 255) / 256, 8192), 256, 0, s>>>(a, b, n);
+  CHNS_HIP(hipGetLastError());
+  return CHNS_OK;
+}
+
+// Exact diagonal of P^T K P.  The scalar operators on octrees in FP64: one
+// pass over the leaves (K_DIAG).  Otherwise by probing: colour classes never
+// share a leaf (directly or through constraint parents), so y = A 1_c has
+// y_i = A_ii on colour c; eight colours on uniform meshes, but about twenty on
+// octrees, where the pass replaces as many applies (35 us each with their
+// helper kernels at levels 5-8).
 int launch_diagonal_lv(Ctx& c, const LevelView& L, int op, int prec, void* d, bool invert, void* xi, void* yi,
                        hipStream_t s) {
   const int64_t n = L.dm->n;
   const int nf = op_fields(op, L.dm->dim);
   const unsigned g = (unsigned)((n + 255) / 256);
   ApplyOut o{};
+  if (!L.dm->structured && prec == CHNS_FP64 &&
+      (op == CHNS_OP_PRESSURE || op == CHNS_OP_MASS || op == CHNS_OP_MASS_RHO || op == CHNS_OP_MOMENTUM_SCALAR)) {
+    if (op != CHNS_OP_MASS && !c.phi_set) {
+      set_error("set_phase_field must be called before this operator");
+      return CHNS_ESTATE;
+    }
+    o.diag_of = op == CHNS_OP_MASS       ? K_MASS
+                : op == CHNS_OP_MASS_RHO ? K_MASS_RHO
+                : op == CHNS_OP_MOMENTUM_SCALAR || c.pp_kind == 1
+                    ? K_VPS
+                    : (c.pp_shift != 0.0 ? K_PPS : K_PP);
+    const double* cf[1] = {L.phi64};
+    int rc = apply_d<K_DIAG, double>(c, L, L.phi64, (double*)d, cf, s, o);
+    if (rc) return rc;
+    k_diag_finish<<<g, 256, 0, s>>>((double*)d, n, nf, op == CHNS_OP_MASS_RHO ? L.dm->wall : nullptr, invert ? 1 : 0);
+    CHNS_HIP(hipGetLastError());
+    return CHNS_OK;
+  }
   // fields of the Cahn-Hilliard Jacobian are coupled: probe them one at a time
   const bool coupled = op == CHNS_OP_CH_JACOBIAN;
   for (int col = 0; col < L.dm->n_colors; ++col) {

@@ -252,6 +252,7 @@ struct ApplyOut {
   const void* sm_r = nullptr;
   const void* sm_dinv = nullptr;
   double sm_w = 0.0;
+  int diag_of = 0;  // one-pass diagonal: the form it is of (apply.hip)
 };
 int launch_apply(Ctx& c, int op, int prec, const void* x, void* y, hipStream_t s, const ApplyOut& o);
 int launch_apply_lv(Ctx& c, const LevelView& L, int op, int prec, const void* x, void* y, hipStream_t s,
@@ -260,6 +261,8 @@ int launch_diagonal(Ctx& c, int op, int prec, void* dinv_or_d, bool invert, hipS
 // probing with caller-provided work vectors xi, yi (n * fields each)
 int launch_diagonal_lv(Ctx& c, const LevelView& L, int op, int prec, void* d, bool invert, void* xi, void* yi,
                        hipStream_t s);
+// b = (float)a
+int launch_narrow(const double* a, float* b, int64_t n, hipStream_t s);
 LevelView fine_view(Ctx& c);
 int op_fields(int op, int dim);
 // device copy of a host mesh (brick tables, combine rows, colours, walls)

@@ -1519,9 +1519,7 @@ int mg_setup(Ctx& c, hipStream_t s) {
       if ((e = launch_diagonal_lv(c, fine_view(c), CHNS_OP_PRESSURE, CHNS_FP64, mg.fine_dinv64, true, c.w64[6],
                                   c.w64[7], st)))
         return e;
-      if ((e = launch_diagonal_lv(c, fine_view(c), CHNS_OP_PRESSURE, CHNS_FP32, mg.fine_dinv32, true, c.w32[6],
-                                  c.w32[7], st)))
-        return e;
+      if ((e = launch_narrow(mg.fine_dinv64, mg.fine_dinv32, c.dm.n, st))) return e;
     }
     const double* phi_f = c.phi64;
     for (size_t k = 1; k < mg.lv.size(); ++k) {
@@ -1569,9 +1567,7 @@ int mg_setup(Ctx& c, hipStream_t s) {
         if ((e = launch_diagonal_lv(c, view(L), CHNS_OP_PRESSURE, CHNS_FP64, L.dinv64, true, L.v64[0], L.v64[3],
                                     st)))
           return e;
-        if ((e = launch_diagonal_lv(c, view(L), CHNS_OP_PRESSURE, CHNS_FP32, L.dinv32, true, L.v32[0], L.v32[3],
-                                    st)))
-          return e;
+        if ((e = launch_narrow(L.dinv64, L.dinv32, nk, st))) return e;
       }
     }
     if (B.S64) {

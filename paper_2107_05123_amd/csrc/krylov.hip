@@ -708,7 +708,7 @@ int solve_pressure_impl(Ctx& c, const double* b_in, double* x_out, const chns_so
       auto diag_part = [&](hipStream_t st) -> int {
         int e = launch_diagonal(c, CHNS_OP_PRESSURE, CHNS_FP64, c.diag64, true, st);
         if (e) return e;
-        return launch_diagonal(c, CHNS_OP_PRESSURE, CHNS_FP32, c.diag32, true, st);
+        return launch_narrow(c.diag64, c.diag32, n, st);
       };
       if ((rc = graphs ? run_captured(c, &c.diag_exec, s, diag_part) : diag_part(s))) return rc;
       c.diag_valid = true;
