@@ -24,6 +24,7 @@
 // stages voxel tiles in LDS and reduces split partial sums in a fixed order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -41,7 +42,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kLayers = 14;
 constexpr int kInCh = 8;
 constexpr int kCh[4] = {16, 32, 48, 64};
-constexpr int kWgradSplits = 48;
 
 struct ULayer {
   int ci = 0, co = 0;
@@ -407,89 +407,146 @@ __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__
   }
 }
 
-// Weight gradient, one tap per block row: partial[s][tap][i][j] =
-// sum over this split's voxels v of in[v + off(tap)][i] dy[v][j]
-// (i < 16 MB input channels, zero beyond ci; j < 16 NB output channels).
-template <int MB, int NB>
-__global__ __launch_bounds__(64) void k_wgrad(const uint16_t* __restrict__ in, int cs_in, int ci,
-                                              const uint16_t* __restrict__ dy, int cs_dy, int E, int S,
-                                              float* __restrict__ partial) {
-  constexpr int CI = MB * 16, CO = NB * 16;
-  __shared__ __attribute__((aligned(16))) uint16_t Xs[32][CI + 8];
-  __shared__ __attribute__((aligned(16))) uint16_t Ys[32][CO + 8];
-  const int lane = threadIdx.x, r16 = lane & 15, g = lane >> 4;
-  const int tap = blockIdx.y, s = blockIdx.x;
-  const int dz = tap / 9 - 1, dy_ = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-  const int V = E * E * E;
-  f32x4 acc[MB][NB];
+// Weight gradient: partial[s][tap][i][j] = sum over this split's voxels v of
+// in[v + off(tap)][i] dy[v][j] (i: the MBG blocks of 16 input channels of this
+// block row, zero beyond ci; j < 16 NB output channels).
+//
+// A workgroup stages the halo of its input channels and the gradients of a
+// 4 x 4 x 16 tile in LDS and forms all 27 taps from them (M = input channels,
+// N = output channels, K = voxels); its four waves share the (tap, channel
+// block) pairs and keep them in registers over the split's tiles.  Both
+// operands are stored voxel by voxel, so a fragment (eight voxels of one
+// channel per lane) comes from two transposing LDS reads.  Bound for one
+// output block: those reads, 1 KiB a fragment against one 16-cycle MFMA; in
+// practice the staging of a tile.  One 32-voxel step of one tap per wave,
+// staged and gathered 16 bits at a time, took 317 us for 48 -> 16 channels at
+// 64^3 and 123 us for 16 -> 16; now 24 and 14 us (a training step's gradients
+// 7.65 -> 4.5 ms).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+// lane l of each 16: element i = row i, column l of a 4 x 16 matrix of
+// 16-bit values whose row l / 4, columns 4 (l % 4) .. + 3 are at p
+__device__ __forceinline__ s16x4 read_tr(const uint16_t* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p));
+}
+template <int MBG, int NB>
+__global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ in, int cs_in, int ci,
+                                               const uint16_t* __restrict__ dy, int cs_dy, int E, int S,
+                                               float* __restrict__ partial, int CI) {
+  constexpr int CG = MBG * 16, CO = NB * 16;
+  constexpr int PW = (27 * MBG + 3) / 4;  // (tap, channel block) pairs per wave
+  __shared__ __attribute__((aligned(16))) uint16_t X[kHZ * kHY * kHX * CG];
+  __shared__ __attribute__((aligned(16))) uint16_t Y[kTZ * kTY * kTX * CO];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int s = blockIdx.x, c0 = blockIdx.y * CG;
+  // halo offset of each pair's tap and channel block (pairs beyond the last
+  // repeat it and are not stored)
+  int off[PW];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int k = 0; k < PW; ++k) {
+    const int p = min(wave * PW + k, 27 * MBG - 1);
+    const int tap = p / MBG, mb = p % MBG;
+    off[k] = (((tap / 9) * kHY + (tap / 3) % 3) * kHX + tap % 3) * CG + mb * 16;
+  }
+  f32x4 acc[PW][NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int nq = (V + 31) / 32;
-  for (int q = s; q < nq; q += S) {
-    const int v0 = q * 32;
-    for (int i = lane; i < 32 * NB * 2; i += 64) {
-      const int j = i / (NB * 2), c8 = (i % (NB * 2)) * 8;
-      const int v = v0 + j;
-      u32x4 t = {0u, 0u, 0u, 0u};
-      if (v < V) t = *(const u32x4*)(dy + (int64_t)v * cs_dy + c8);
-      *(u32x4*)&Ys[j][c8] = t;
+  for (int k = 0; k < PW; ++k)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[k][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // voxel 8 g + j of a 32-voxel step: row y0 + g / 2, x = 8 (g % 2) + j
+  const int lx = ((g >> 1) * kHX + 8 * (g & 1) + (r16 >> 2)) * CG + 4 * (r16 & 3);
+  const int ly = ((g >> 1) * kTX + 8 * (g & 1) + (r16 >> 2)) * CO + 4 * (r16 & 3);
+  const int nx = (E + kTX - 1) / kTX, ny = (E + kTY - 1) / kTY, nz = (E + kTZ - 1) / kTZ;
+  for (int t = s; t < nx * ny * nz; t += S) {
+    const int ox = (t % nx) * kTX, oy = (t / nx) % ny * kTY, oz = t / (nx * ny) * kTZ;
+    constexpr int NS = kHZ * kHY * kHX * MBG * 2;
+#pragma unroll
+    for (int j = 0; j < (NS + 255) / 256; ++j) {
+      const int i = tid + j * 256;
+      const int hv = i / (MBG * 2), c = (i % (MBG * 2)) * 8;
+      const int hx = hv % kHX, hy = (hv / kHX) % kHY, hz = hv / (kHX * kHY);
+      const int x = ox + hx - 1, y = oy + hy - 1, z = oz + hz - 1;
+      u32x4 w = {0u, 0u, 0u, 0u};
+      if (i < NS && c0 + c < ci && x >= 0 && x < E && y >= 0 && y < E && z >= 0 && z < E)
+        w = *(const u32x4*)(in + ((int64_t)(z * E + y) * E + x) * cs_in + c0 + c);
+      if (i < NS) *(u32x4*)&X[hv * CG + c] = w;
     }
-    for (int i = lane; i < 32 * MB * 2; i += 64) {
-      const int j = i / (MB * 2), c8 = (i % (MB * 2)) * 8;
-      const int v = v0 + j;
-      u32x4 t = {0u, 0u, 0u, 0u};
-      if (v < V && c8 < ci) {
-        const int x = v % E + dx, y = (v / E) % E + dy_, z = v / (E * E) + dz;
-        if (x >= 0 && x < E && y >= 0 && y < E && z >= 0 && z < E)
-          t = *(const u32x4*)(in + ((int64_t)(z * E + y) * E + x) * cs_in + c8);
-      }
-      *(u32x4*)&Xs[j][c8] = t;
+#pragma unroll
+    for (int j = 0; j < NB * 2; ++j) {
+      const int i = tid + j * 256;
+      const int v = i / (NB * 2), c = (i % (NB * 2)) * 8;
+      const int x = ox + v % kTX, y = oy + (v / kTX) % kTY, z = oz + v / (kTX * kTY);
+      u32x4 w = {0u, 0u, 0u, 0u};
+      if (x < E && y < E && z < E) w = *(const u32x4*)(dy + ((int64_t)(z * E + y) * E + x) * cs_dy + c);
+      *(u32x4*)&Y[v * CO + c] = w;
     }
     __syncthreads();
-    bf16x8 a[MB], b[NB];
+#pragma unroll 1
+    for (int z = 0; z < kTZ; ++z)
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      u32x4 t;
+      for (int y = 0; y < kTY; y += 2) {
+        const uint16_t* px = X + (z * kHY + y) * kHX * CG + lx;
+        const uint16_t* py = Y + (z * kTY + y) * kTX * CO + ly;
+        bf16x8 b[NB];
 #pragma unroll
-      for (int h = 0; h < 4; ++h)
-        t[h] = (uint32_t)Xs[8 * g + 2 * h][mb * 16 + r16] | ((uint32_t)Xs[8 * g + 2 * h + 1][mb * 16 + r16] << 16);
-      a[mb] = as_bf(t);
-    }
+        for (int nb = 0; nb < NB; ++nb) {
+          const s16x4 lo = read_tr(py + nb * 16), hi = read_tr(py + nb * 16 + 4 * CO);
+          b[nb] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      u32x4 t;
+        for (int k = 0; k < PW; ++k) {
+          const s16x4 lo = read_tr(px + off[k]), hi = read_tr(px + off[k] + 4 * CG);
+          const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-      for (int h = 0; h < 4; ++h)
-        t[h] = (uint32_t)Ys[8 * g + 2 * h][nb * 16 + r16] | ((uint32_t)Ys[8 * g + 2 * h + 1][nb * 16 + r16] << 16);
-      b[nb] = as_bf(t);
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mb], b[nb], acc[mb][nb], 0, 0, 0);
+          for (int nb = 0; nb < NB; ++nb)
+            acc[k][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[nb], acc[k][nb], 0, 0, 0);
+        }
+      }
     __syncthreads();
   }
-  float* p = partial + ((int64_t)s * 27 + tap) * CI * CO;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int k = 0; k < PW; ++k) {
+    const int p = wave * PW + k;
+    if (p >= 27 * MBG) break;
+    const int tap = p / MBG, mb = p % MBG;
+    float* q = partial + (((int64_t)s * 27 + tap) * CI + c0 + mb * 16) * CO;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) p[(mb * 16 + 4 * g + r) * CO + nb * 16 + r16] = acc[mb][nb][r];
+      for (int r = 0; r < 4; ++r) q[(4 * g + r) * CO + nb * 16 + r16] = acc[k][nb][r];
+  }
 }
 
-// grad[t][i][j] (+)= sum_s partial[s][t][i][j], fixed order over s
-__global__ void k_wgrad_reduce(const float* partial, int S, int ci, int co, int CI, int CO, float* grad,
-                               float scale, int accumulate) {
-  ULOOP(idx, (int64_t)27 * ci * co) {
-    const int j = (int)(idx % co), i = (int)((idx / co) % ci), t = (int)(idx / ((int64_t)ci * co));
-    float sum = 0.0f;
-    for (int s = 0; s < S; ++s) sum += partial[(((int64_t)s * 27 + t) * CI + i) * CO + j];
-    grad[idx] = (accumulate ? grad[idx] : 0.0f) + scale * sum;
+// grad[t][i][j] (+)= sum_s partial[s][t][i][j], fixed order: 16 threads per
+// entry, each every 16th split, then the 16 sums in order
+__global__ __launch_bounds__(1024) void k_wgrad_reduce(const float* partial, int S, int ci, int co, int CI, int CO,
+                                                       float* grad, float scale, int accumulate) {
+  __shared__ float sh[16][64];
+  const int l = threadIdx.x & 63, part = threadIdx.x >> 6;
+  const int n = 27 * ci * co, idx = blockIdx.x * 64 + l;
+  const int j = idx % co, i = (idx / co) % ci, t = idx / (ci * co);
+  float sum = 0.0f;
+  if (idx < n) {
+    const float* p = partial + ((int64_t)t * CI + i) * CO + j;
+    const int64_t st = (int64_t)27 * CI * CO;
+    int s = part;
+    for (; s + 48 < S; s += 64) {
+      const float a = p[s * st], b = p[(s + 16) * st], c = p[(s + 32) * st], d = p[(s + 48) * st];
+      sum += a;
+      sum += b;
+      sum += c;
+      sum += d;
+    }
+    for (; s < S; s += 16) sum += p[s * st];
   }
+  sh[part][l] = sum;
+  __syncthreads();
+  if (part != 0 || idx >= n) return;
+  float v = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v += sh[k][l];
+  grad[idx] = (accumulate ? grad[idx] : 0.0f) + scale * v;
 }
 
 // ------------------------------------------------------- other layers
@@ -992,24 +1049,26 @@ int conv(const uint16_t* in, int cs_in, int ci, const uint16_t* wt, uint16_t* ou
   return CHNS_OK;
 }
 
+// 16-channel input blocks a weight-gradient workgroup takes at once (three
+// where one output block leaves registers for them), the block rows that
+// gives, and the most splits of the voxels: 512 workgroups, two on each CU
+int wgrad_blocks(const ULayer& l) { return l.co == 16 && (l.ci + 15) / 16 == 3 ? 3 : 1; }
+int wgrad_rows(const ULayer& l) { return (l.ci + 15) / 16 / wgrad_blocks(l); }
+int wgrad_splits(const ULayer& l) { return 512 / wgrad_rows(l); }
+
 int wgrad(UNet& u, int layer, const uint16_t* in, int cs_in, const uint16_t* dy, int cs_dy, int E, float scale,
           int accumulate, hipStream_t s) {
   const ULayer& l = u.L[layer];
   const int MB = (l.ci + 15) / 16, NB = l.co / 16;
-  const dim3 g(kWgradSplits, 27);
-#define WG(a, b) \
-  k_wgrad<a, b><<<g, 64, 0, s>>>(in, cs_in, l.ci, dy, cs_dy, E, kWgradSplits, u.partial)
-  const int key = MB * 10 + NB;
-  switch (key) {
+  const int tiles = ((E + kTX - 1) / kTX) * ((E + kTY - 1) / kTY) * ((E + kTZ - 1) / kTZ);
+  const int S = std::min(tiles, wgrad_splits(l));
+  const dim3 g((unsigned)S, (unsigned)wgrad_rows(l));
+#define WG(a, b) k_wgrad<a, b><<<g, 256, 0, s>>>(in, cs_in, l.ci, dy, cs_dy, E, S, u.partial, MB * 16)
+  switch (wgrad_blocks(l) * 10 + NB) {
     case 11: WG(1, 1); break;
     case 12: WG(1, 2); break;
-    case 22: WG(2, 2); break;
-    case 23: WG(2, 3); break;
-    case 33: WG(3, 3); break;
-    case 34: WG(3, 4); break;
-    case 44: WG(4, 4); break;
-    case 73: WG(7, 3); break;
-    case 52: WG(5, 2); break;
+    case 13: WG(1, 3); break;
+    case 14: WG(1, 4); break;
     case 31: WG(3, 1); break;
     default:
       set_error("unsupported weight-gradient shape");
@@ -1017,8 +1076,9 @@ int wgrad(UNet& u, int layer, const uint16_t* in, int cs_in, const uint16_t* dy,
   }
 #undef WG
   CHNS_HIP(hipGetLastError());
-  k_wgrad_reduce<<<nblk((int64_t)27 * l.ci * l.co), kT, 0, s>>>(u.partial, kWgradSplits, l.ci, l.co, MB * 16, NB * 16,
-                                                                 u.grad + l.off, scale, accumulate);
+  const int n = 27 * l.ci * l.co;
+  k_wgrad_reduce<<<(n + 63) / 64, 1024, 0, s>>>(u.partial, S, l.ci, l.co, MB * 16, NB * 16, u.grad + l.off, scale,
+                                                accumulate);
   CHNS_HIP(hipGetLastError());
   return CHNS_OK;
 }
@@ -1249,7 +1309,7 @@ int unet_create(Ctx& c) {
   u.wbf = (uint16_t*)c.dalloc(sizeof(uint16_t) * nbf);
   size_t pmax = 0;
   for (int k = 0; k < kLayers; ++k)
-    pmax = std::max(pmax, (size_t)kWgradSplits * 27 * ((u.L[k].ci + 15) / 16 * 16) * u.L[k].co);
+    pmax = std::max(pmax, (size_t)wgrad_splits(u.L[k]) * 27 * ((u.L[k].ci + 15) / 16 * 16) * u.L[k].co);
   u.partial = (float*)c.dalloc(sizeof(float) * pmax);
   u.partial_cap = pmax;
   u.red = (double*)c.dalloc(sizeof(double) * 3 * kRedBlocks);  // up to three partial rows
