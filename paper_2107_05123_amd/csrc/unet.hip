@@ -148,35 +148,42 @@ inline unsigned nblk(int64_t n) {
 // channels the (4+2) x (4+2) x (16+2) halo is loaded once (16-byte rows,
 // zero outside the grid and beyond ci) and the 27 taps read it from LDS.
 // Wave w computes the z-slice w of the tile: four 16-voxel rows (one per y)
-// times NB 16-channel column blocks.
+// times NB 16-channel column blocks, NB of the layer's parts * NB.
+// Channels below ci_up come from the half-resolution grid `up` (each voxel
+// copied to its 2 x 2 x 2 children), the others from `in`: the upsampled half
+// of a concatenation is read where it is instead of being written out first.
 constexpr int kTX = 16, kTY = 4, kTZ = 4;
 
-// Output tile of a convolution workgroup.  Workgroups are dealt round-robin
+// Output tile of a convolution workgroup, and which of the layer's `parts`
+// shares of the output channels it forms.  Workgroups are dealt round-robin
 // to the 8 XCDs (linear id b on XCD b % 8, each XCD with its own L2); the
 // linear id is remapped so that each XCD runs a contiguous run of tiles (a
 // slab of the grid), whose overlapping halos then meet in one L2.
-__device__ __forceinline__ void conv_tile(int& ox, int& oy, int& oz) {
+__device__ __forceinline__ int conv_tile(int& ox, int& oy, int& oz, int parts) {
   constexpr uint32_t kXcd = 8;
   const uint32_t gx = gridDim.x, gy = gridDim.y, g = gx * gy * gridDim.z;
   const uint32_t b = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
   const uint32_t per = g / kXcd, rem = g % kXcd, x = b % kXcd;
-  const uint32_t t = x * per + (x < rem ? x : rem) + b / kXcd;
+  const uint32_t u = x * per + (x < rem ? x : rem) + b / kXcd, t = u / parts;
   ox = (int)(t % gx) * kTX;
   oy = (int)((t / gx) % gy) * kTY;
   oz = (int)(t / (gx * gy)) * kTZ;
+  return (int)(u % parts);
 }
 constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2;
 constexpr int kHRow = 40;  // bf16 per halo voxel: 32 channels + 8 padding (bank spread)
 template <int NB>
 __global__ __launch_bounds__(256) void k_conv3_tile(const uint16_t* __restrict__ in, int cs_in, int ci,
+                                                    const uint16_t* __restrict__ up, int cs_up, int ci_up,
                                                     const uint16_t* __restrict__ wt, uint16_t* __restrict__ out,
-                                                    int cs_out, int E, int relu) {
+                                                    int cs_out, int parts, int E, int relu) {
   __shared__ __attribute__((aligned(16))) uint16_t H[kHZ * kHY * kHX * kHRow];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, g = lane >> 4;
-  const int co = NB * 16;
+  const int co = NB * 16 * parts;
   int ox, oy, oz;
-  conv_tile(ox, oy, oz);
+  const int n0 = conv_tile(ox, oy, oz, parts) * NB * 16;
+  wt += (int64_t)n0 * ci;
   f32x4 acc[4][NB];
 #pragma unroll
   for (int mb = 0; mb < 4; ++mb)
@@ -196,8 +203,11 @@ __global__ __launch_bounds__(256) void k_conv3_tile(const uint16_t* __restrict__
       const int x = ox + hx - 1, y = oy + hy - 1, z = oz + hz - 1;
       const int k = c * 32 + part * 8;
       t[j] = u32x4{0u, 0u, 0u, 0u};
-      if (i < NS && k < ci && x >= 0 && x < E && y >= 0 && y < E && z >= 0 && z < E)
-        t[j] = *(const u32x4*)(in + ((int64_t)(z * E + y) * E + x) * cs_in + k);
+      if (i < NS && k < ci && x >= 0 && x < E && y >= 0 && y < E && z >= 0 && z < E) {
+        const int h = E / 2;
+        t[j] = *(const u32x4*)(k < ci_up ? up + ((int64_t)((z / 2) * h + y / 2) * h + x / 2) * cs_up + k
+                                         : in + ((int64_t)(z * E + y) * E + x) * cs_in + k);
+      }
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
@@ -291,7 +301,7 @@ __global__ __launch_bounds__(256) void k_conv3_tile(const uint16_t* __restrict__
       for (int nb = 0; nb < NB; ++nb) {
         float val = acc[mb][nb][r];
         if (relu) val = fmaxf(val, 0.0f);
-        out[v * cs_out + nb * 16 + r16] = f2bf(val);
+        out[v * cs_out + n0 + nb * 16 + r16] = f2bf(val);
       }
     }
   }
@@ -305,7 +315,7 @@ __global__ __launch_bounds__(256) void k_conv3_tile(const uint16_t* __restrict__
 template <int NB, int CI>
 __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__ in, int cs_in,
                                                     const uint16_t* __restrict__ wt, uint16_t* __restrict__ out,
-                                                    int cs_out, int E, int relu) {
+                                                    int cs_out, int parts, int E, int relu) {
   constexpr int ROW = CI + 8;  // bf16 per halo voxel (8 padding: bank spread, 16-byte rows)
   constexpr int PARTS = CI / 8;
   constexpr int KT = 27 * CI;
@@ -314,9 +324,10 @@ __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__
   __shared__ __attribute__((aligned(16))) uint16_t H[kHZ * kHY * kHX * ROW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, g = lane >> 4;
-  const int co = NB * 16;
+  const int co = NB * 16 * parts;
   int ox, oy, oz;
-  conv_tile(ox, oy, oz);
+  const int n0 = conv_tile(ox, oy, oz, parts) * NB * 16;
+  wt += (int64_t)n0 * CI;
   if constexpr (CI >= 32) {
     // all loads of a thread before its first LDS store (measured faster
     // for 32 and 48 channels; for 16 the unrolled loads cost occupancy); the
@@ -401,7 +412,7 @@ __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__
       for (int nb = 0; nb < NB; ++nb) {
         float val = acc[mb][nb][r];
         if (relu) val = fmaxf(val, 0.0f);
-        out[v * cs_out + nb * 16 + r16] = f2bf(val);
+        out[v * cs_out + n0 + nb * 16 + r16] = f2bf(val);
       }
     }
   }
@@ -420,8 +431,8 @@ __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__
 // output block: those reads, 1 KiB a fragment against one 16-cycle MFMA; in
 // practice the staging of a tile.  One 32-voxel step of one tap per wave,
 // staged and gathered 16 bits at a time, took 317 us for 48 -> 16 channels at
-// 64^3 and 123 us for 16 -> 16; now 24 and 14 us (a training step's gradients
-// 7.65 -> 4.5 ms).
+// 64^3 and 123 us for 16 -> 16; now 57 and 15.5 us (a training step's gradients
+// 7.66 -> 4.21 ms).
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 // lane l of each 16: element i = row i, column l of a 4 x 16 matrix of
@@ -1016,16 +1027,25 @@ __global__ void k_gbeta(double* gn, const double* G, const double* r1, const dou
 }
 
 // ------------------------------------------------------------ host side
+// up (or null): channels below ci_up read from the half-resolution grid.
+// A workgroup forms all output channels of its tile while there are tiles
+// enough for the chip (a fragment then feeds every column block); on the small
+// grids each 16-channel block gets a workgroup of its own (E = 16, 64 -> 64
+// channels: 16 workgroups, 30 us; 64, 14 us).  The order of the sums is the
+// same either way.
 int conv(const uint16_t* in, int cs_in, int ci, const uint16_t* wt, uint16_t* out, int cs_out, int co, int E,
-         bool relu, hipStream_t s) {
+         bool relu, hipStream_t s, const uint16_t* up = nullptr, int cs_up = 0, int ci_up = 0) {
   const int r = relu ? 1 : 0;
-  const dim3 g((unsigned)((E + kTX - 1) / kTX), (unsigned)((E + kTY - 1) / kTY), (unsigned)((E + kTZ - 1) / kTZ));
-  const int key = (co / 16) * 100 + ci;
-  if (ci == 8 || ci == 16 || ci == 32 || key == 348) {
+  const unsigned tx = (unsigned)((E + kTX - 1) / kTX), ty = (unsigned)((E + kTY - 1) / kTY),
+                 tz = (unsigned)((E + kTZ - 1) / kTZ);
+  const int nb = co / 16, parts = tx * ty * tz < 256 ? nb : 1;
+  const dim3 g(tx, ty, tz * parts);
+  const int key = nb / parts * 100 + ci;
+  if (!up && (ci == 8 || ci == 16 || ci == 32 || (ci == 48 && nb == 3))) {
     switch (key) {
-#define FL(nb, cc) \
-  case nb * 100 + cc: k_conv3_flat<nb, cc><<<g, 256, 0, s>>>(in, cs_in, wt, out, cs_out, E, r); break;
-      FL(1, 8) FL(1, 16) FL(1, 32) FL(2, 16) FL(2, 32) FL(3, 32) FL(5, 32) FL(3, 16) FL(3, 48)
+#define FL(b, cc) \
+  case b * 100 + cc: k_conv3_flat<b, cc><<<g, 256, 0, s>>>(in, cs_in, wt, out, cs_out, parts, E, r); break;
+      FL(1, 8) FL(1, 16) FL(1, 32) FL(1, 48) FL(2, 16) FL(2, 32) FL(3, 32) FL(5, 32) FL(3, 16) FL(3, 48)
 #undef FL
       default:
         set_error("unsupported channel count");
@@ -1034,13 +1054,11 @@ int conv(const uint16_t* in, int cs_in, int ci, const uint16_t* wt, uint16_t* ou
     CHNS_HIP(hipGetLastError());
     return CHNS_OK;
   }
-  switch (co / 16) {
-    case 1: k_conv3_tile<1><<<g, 256, 0, s>>>(in, cs_in, ci, wt, out, cs_out, E, r); break;
-    case 2: k_conv3_tile<2><<<g, 256, 0, s>>>(in, cs_in, ci, wt, out, cs_out, E, r); break;
-    case 3: k_conv3_tile<3><<<g, 256, 0, s>>>(in, cs_in, ci, wt, out, cs_out, E, r); break;
-    case 4: k_conv3_tile<4><<<g, 256, 0, s>>>(in, cs_in, ci, wt, out, cs_out, E, r); break;
-    case 5: k_conv3_tile<5><<<g, 256, 0, s>>>(in, cs_in, ci, wt, out, cs_out, E, r); break;
-    case 7: k_conv3_tile<7><<<g, 256, 0, s>>>(in, cs_in, ci, wt, out, cs_out, E, r); break;
+  switch (nb / parts) {
+#define TL(b) \
+  case b: k_conv3_tile<b><<<g, 256, 0, s>>>(in, cs_in, ci, up, cs_up, ci_up, wt, out, cs_out, parts, E, r); break;
+    TL(1) TL(2) TL(3) TL(4) TL(5) TL(7)
+#undef TL
     default:
       set_error("unsupported channel count");
       return CHNS_EINVAL;
@@ -1156,6 +1174,12 @@ int forward(UNet& u, UActs& a, hipStream_t s) {
   int rc;
 #define CV(in, csi, k, out, cso, E) \
   if ((rc = conv(in, csi, L[k].ci, L[k].wf, out, cso, L[k].co, E, true, s))) return rc;
+  // the first convolution after a concatenation reads its upsampled channels
+  // from the coarse grid; with gradients to come the weight gradient needs
+  // them in place
+#define CU(low, cu, cat, csi, k, out, cso, E)                                                                     \
+  if (a.grads) k_up<<<nblk((int64_t)(E) * (E) * (E) * (cu) / 8), kT, 0, s>>>(low, cu, cat, csi, E);               \
+  if ((rc = conv(cat, csi, L[k].ci, L[k].wf, out, cso, L[k].co, E, true, s, low, cu, cu))) return rc;
   CV(a.X, kInCh, 0, a.A0, 16, E0);
   CV(a.A0, 16, 1, a.cat0 + 32, 48, E0);
   k_pool<<<nblk((int64_t)E1 * E1 * E1 * 2), kT, 0, s>>>(a.cat0 + 32, 48, a.P0, 16, E1);
@@ -1167,16 +1191,14 @@ int forward(UNet& u, UActs& a, hipStream_t s) {
   k_pool<<<nblk((int64_t)E3 * E3 * E3 * 6), kT, 0, s>>>(a.cat2 + 64, 112, a.P2, 48, E3);
   CV(a.P2, 48, 6, a.A6, 64, E3);
   CV(a.A6, 64, 7, a.A7, 64, E3);
-  k_up<<<nblk((int64_t)E2 * E2 * E2 * 8), kT, 0, s>>>(a.A7, 64, a.cat2, 112, E2);
-  CV(a.cat2, 112, 8, a.A8, 48, E2);
+  CU(a.A7, 64, a.cat2, 112, 8, a.A8, 48, E2);
   CV(a.A8, 48, 9, a.A9, 48, E2);
-  k_up<<<nblk((int64_t)E1 * E1 * E1 * 6), kT, 0, s>>>(a.A9, 48, a.cat1, 80, E1);
-  CV(a.cat1, 80, 10, a.A10, 32, E1);
+  CU(a.A9, 48, a.cat1, 80, 10, a.A10, 32, E1);
   CV(a.A10, 32, 11, a.A11, 32, E1);
-  k_up<<<nblk((int64_t)E0 * E0 * E0 * 4), kT, 0, s>>>(a.A11, 32, a.cat0, 48, E0);
-  CV(a.cat0, 48, 12, a.A12, 16, E0);
+  CU(a.A11, 32, a.cat0, 48, 12, a.A12, 16, E0);
   CV(a.A12, 16, 13, a.A13, 16, E0);
 #undef CV
+#undef CU
   CHNS_HIP(hipGetLastError());
   return CHNS_OK;
 }
