@@ -17,6 +17,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <vector>
 
 #include "chns_internal.h"
@@ -31,6 +32,7 @@ constexpr int kMaxBlocks = 512;
 // (upper-triangular) column of the Hessenberg matrix.
 struct GmDev {
   int j, m, done, conv;  // completed Arnoldi steps, restart length, flags
+  int jc, pad;           // the step under way (k_gms_*: while j moves on)
   double tol, hinv, ww, beta;
   double g[kGmMax + 1], cs[kGmMax], sn[kGmMax], y[kGmMax];
   double h1[kGmMax + 1], h2[kGmMax + 1];
@@ -53,6 +55,8 @@ struct Stepper {
   double* red = nullptr;   // reduction results (device)
   GmDev* gd = nullptr;
   GmDev* gd_host = nullptr;  // pinned
+  // pinned {done, j}: stored by the kernel that ends an Arnoldi step
+  int* gm_flag = nullptr;
   double* red_host = nullptr;  // pinned
   hipEvent_t ev[4] = {};
   struct Graph {
@@ -255,40 +259,57 @@ __global__ __launch_bounds__(kT) void k_gm_orth(const double* V, int64_t nv, dou
     if (threadIdx.x == 0) part[blockIdx.x] = ww;
   }
 }
-// new Hessenberg column, Givens rotations, residual estimate, flags
-__global__ __launch_bounds__(kT) void k_gm_givens(const double* part, int np, GmDev* gd) {
+// New Hessenberg column (h1 + h2, norm hn), Givens rotations, residual
+// estimate and flags, by one block: the column and the rotations are read into
+// LDS together, then one thread runs the chain of rotations.
+__device__ void gm_column(GmDev* gd, int j, double hn, int* flag) {
+  __shared__ double h[kGmMax + 1], cs[kGmMax], sn[kGmMax], out[kGmMax];
+  const int M1 = gd->m + 1, t = threadIdx.x;
+  if (t <= j) h[t] = gd->h1[t] + gd->h2[t];
+  if (t < j) {
+    cs[t] = gd->cs[t];
+    sn[t] = gd->sn[t];
+  }
+  __syncthreads();
+  double* col = gd->H + (int64_t)j * M1;
+  if (t == 0) {
+    double a = h[0];
+#pragma unroll 8
+    for (int k = 0; k < j; ++k) {
+      const double b = h[k + 1];
+      out[k] = cs[k] * a + sn[k] * b;
+      a = -sn[k] * a + cs[k] * b;
+    }
+    const double r = hypot(a, hn);
+    const double c = r > 0.0 ? a / r : 1.0, s = r > 0.0 ? hn / r : 0.0;
+    gd->cs[j] = c;
+    gd->sn[j] = s;
+    col[j] = r;
+    col[j + 1] = 0.0;
+    const double gj = gd->g[j], gn = -s * gj;
+    gd->g[j + 1] = gn;
+    gd->g[j] = c * gj;
+    gd->j = j + 1;
+    gd->hinv = hn > 0.0 ? 1.0 / hn : 0.0;
+    const bool conv = fabs(gn) <= gd->tol;
+    const bool done = conv || j + 1 >= gd->m || !(hn > 0.0);
+    if (conv) gd->conv = 1;
+    // vector stores with system scope into pinned host memory; visible to
+    // the host once an event recorded after this kernel has completed
+    __hip_atomic_store(&flag[1], j + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&flag[0], done ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (done) gd->done = 1;
+  }
+  __syncthreads();
+  if (t < j) col[t] = out[t];
+}
+__global__ __launch_bounds__(kT) void k_gm_givens(const double* part, int np, GmDev* gd, int* flag) {
   __shared__ double sh[4];
   if (gd->done) return;
   double v = 0.0;
   for (int t = threadIdx.x; t < np; t += kT) v += part[t];
   v = bsum(v, sh);
-  if (threadIdx.x != 0) return;
-  const int j = gd->j, M1 = gd->m + 1;
-  const double hn = sqrt(v);
-  double* col = gd->H + (int64_t)j * M1;
-  for (int k = 0; k <= j; ++k) col[k] = gd->h1[k] + gd->h2[k];
-  col[j + 1] = hn;
-  for (int k = 0; k < j; ++k) {
-    const double a = col[k], b = col[k + 1];
-    col[k] = gd->cs[k] * a + gd->sn[k] * b;
-    col[k + 1] = -gd->sn[k] * a + gd->cs[k] * b;
-  }
-  const double a = col[j], b = col[j + 1];
-  const double r = hypot(a, b);
-  const double c = r > 0.0 ? a / r : 1.0, s = r > 0.0 ? b / r : 0.0;
-  gd->cs[j] = c;
-  gd->sn[j] = s;
-  col[j] = r;
-  col[j + 1] = 0.0;
-  gd->g[j + 1] = -s * gd->g[j];
-  gd->g[j] = c * gd->g[j];
-  gd->j = j + 1;
-  gd->hinv = hn > 0.0 ? 1.0 / hn : 0.0;
-  if (fabs(gd->g[j + 1]) <= gd->tol) {
-    gd->conv = 1;
-    gd->done = 1;
-  }
-  if (j + 1 >= gd->m || !(hn > 0.0)) gd->done = 1;
+  gm_column(gd, gd->j, sqrt(v), flag);
 }
 // V_j = w / |w| (j already advanced)
 __global__ void k_gm_scale(double* V, int64_t nv, const double* w, const GmDev* gd) {
@@ -296,6 +317,182 @@ __global__ void k_gm_scale(double* V, int64_t nv, const double* w, const GmDev* 
   double* out = V + (int64_t)gd->j * nv;
   const double s = gd->hinv;
   GRID_LOOP(i, nv) out[i] = w[i] * s;
+}
+// ---- Arnoldi step of a small system (up to kSmallNv unknowns) in four
+// kernels after the apply: a 2D 64 x 64 step makes about two hundred of them,
+// and at this size a kernel is its launch and one or two chains of dependent
+// loads (3.5 to 9 us), so the one-block reductions between the vector kernels
+// are formed by their consumers, in every block and in one fixed order, and
+// neighbouring passes over the same elements share a kernel: dots, first
+// orthogonalisation with the second dots, second orthogonalisation with the
+// norm, and the new basis vector with the rotations and the next
+// preconditioner application.  Nine kernels an iteration -> four.
+constexpr int kSmallNv = 65536;
+constexpr int kSmallBlocks = 128;
+constexpr int kSmallEpt = kSmallNv / (kSmallBlocks * kT);  // elements per thread
+
+// totals of 16 values over a wave: value v in lanes with
+// (lane & 15) = bit-reversed v (four halving steps, then two plain ones)
+__device__ __forceinline__ double wsum16(double (&a)[16], int lane) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int half = 8 >> s;
+    const bool up = (lane >> s) & 1;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (i < half) {
+        const double keep = up ? a[i + half] : a[i], send = up ? a[i] : a[i + half];
+        a[i] = keep + __shfl_xor(send, 1 << s, 64);
+      }
+  }
+  double t = a[0];
+  t += __shfl_xor(t, 16, 64);
+  t += __shfl_xor(t, 32, 64);
+  return t;
+}
+// part[block][k] = sum over the block's elements of V_k t, k <= j
+template <int EPT>
+__device__ __forceinline__ void small_dots(const double* V, int64_t nv, int j, const double (&t)[EPT],
+                                           const int (&idx)[EPT], double* part) {
+  __shared__ double red[4][kGmMax + 16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  for (int k0 = 0; k0 <= j; k0 += 16) {
+    double a[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      a[q] = 0.0;
+#pragma unroll
+      for (int e = 0; e < EPT; ++e)
+        if (k0 + q <= j && idx[e] < nv) a[q] += V[(int64_t)(k0 + q) * nv + idx[e]] * t[e];
+    }
+    const double s = wsum16(a, lane);
+    if (lane < 16) red[w][k0 + (int)(__brev((unsigned)lane) >> 28)] = s;
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k <= j; k += kT)
+    part[(int64_t)blockIdx.x * (kGmMax + 1) + k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
+}
+// hs[k] = sum over np blocks of part[block][k], k <= j
+__device__ __forceinline__ void small_total(const double* part, int np, int j, double* hs) {
+  __shared__ double half[kGmMax];
+  const int k = threadIdx.x & 127, h = threadIdx.x >> 7, mid = np / 2;
+  double v = 0.0;
+  if (k <= j && k < 128) {
+    const int b0 = h ? mid : 0, b1 = h ? np : mid;
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) v += part[(int64_t)b * (kGmMax + 1) + k];
+  }
+  if (h) half[k] = v;
+  __syncthreads();
+  if (!h) hs[k] = v + half[k];
+  __syncthreads();
+}
+template <int EPT>
+__device__ __forceinline__ void small_index(int (&idx)[EPT]) {
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) idx[e] = (e * gridDim.x + blockIdx.x) * kT + threadIdx.x;
+}
+// t = w - sum_k hs[k] V_k
+template <int EPT>
+__device__ __forceinline__ void small_orth(const double* V, int64_t nv, int j, const double* w, const double* hs,
+                                           const int (&idx)[EPT], double (&t)[EPT]) {
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    t[e] = 0.0;
+    if (idx[e] >= nv) continue;
+    t[e] = w[idx[e]];
+#pragma unroll 8
+    for (int k = 0; k <= j; ++k) t[e] -= hs[k] * V[(int64_t)k * nv + idx[e]];
+  }
+}
+__global__ __launch_bounds__(kT) void k_gms_dots(const double* V, int64_t nv, const double* w, const GmDev* gd,
+                                                 double* part) {
+  if (gd->done) return;
+  int idx[kSmallEpt];
+  double t[kSmallEpt];
+  small_index(idx);
+#pragma unroll
+  for (int e = 0; e < kSmallEpt; ++e) t[e] = idx[e] < nv ? w[idx[e]] : 0.0;
+  small_dots(V, nv, gd->j, t, idx, part);
+}
+__global__ __launch_bounds__(kT) void k_gms_orth1(const double* V, int64_t nv, double* w, GmDev* gd,
+                                                  const double* part, double* part2) {
+  __shared__ double hs[kGmMax];
+  if (gd->done) return;
+  const int j = gd->j;
+  small_total(part, gridDim.x, j, hs);
+  if (blockIdx.x == 0 && threadIdx.x <= j) gd->h1[threadIdx.x] = hs[threadIdx.x];
+  int idx[kSmallEpt];
+  double t[kSmallEpt];
+  small_index(idx);
+  small_orth(V, nv, j, w, hs, idx, t);
+#pragma unroll
+  for (int e = 0; e < kSmallEpt; ++e)
+    if (idx[e] < nv) w[idx[e]] = t[e];
+  small_dots(V, nv, j, t, idx, part2);
+}
+__global__ __launch_bounds__(kT) void k_gms_orth2(const double* V, int64_t nv, double* w, GmDev* gd,
+                                                  const double* part2, double* part) {
+  __shared__ double hs[kGmMax];
+  __shared__ double sh[4];
+  if (gd->done) return;
+  const int j = gd->j;
+  small_total(part2, gridDim.x, j, hs);
+  if (blockIdx.x == 0) {
+    if (threadIdx.x <= j) gd->h2[threadIdx.x] = hs[threadIdx.x];
+    if (threadIdx.x == 0) gd->jc = j;
+  }
+  int idx[kSmallEpt];
+  double t[kSmallEpt], ww = 0.0;
+  small_index(idx);
+  small_orth(V, nv, j, w, hs, idx, t);
+#pragma unroll
+  for (int e = 0; e < kSmallEpt; ++e)
+    if (idx[e] < nv) {
+      w[idx[e]] = t[e];
+      ww += t[e] * t[e];
+    }
+  ww = bsum(ww, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = ww;
+}
+// z = M^-1 v of a pointwise preconditioner
+__device__ __forceinline__ void small_pc(const double* v, double s, int64_t nv, int64_t n, double* out, double* z,
+                                         int pc, const double* pcd) {
+  if (pc == GPC_BLOCK2) {
+    GRID_LOOP(i, n) {
+      const double a = v[i] * s, b = v[n + i] * s;
+      out[i] = a;
+      out[n + i] = b;
+      z[i] = pcd[i] * a + pcd[n + i] * b;
+      z[n + i] = pcd[2 * n + i] * a + pcd[3 * n + i] * b;
+    }
+  } else {
+    GRID_LOOP(i, nv) {
+      const double a = v[i] * s;
+      out[i] = a;
+      if (pc == GPC_JACOBI) z[i] = pcd[i] * a;
+      else if (pc == GPC_NONE) z[i] = a;
+    }
+  }
+}
+// V_{j+1} = w / |w| and z = M^-1 V_{j+1} (pointwise preconditioners); the
+// first block also ends the step (gm_column), after reading nothing that
+// another block still needs: those take the step's number from jc, and one
+// that already sees the end of the cycle has no vector left to write
+__global__ __launch_bounds__(kT) void k_gms_next(double* V, int64_t nv, int64_t n, const double* w, double* z,
+                                                 GmDev* gd, int pc, const double* pcd, const double* part, int np,
+                                                 int* flag) {
+  __shared__ double sh[4];
+  __shared__ int over;
+  if (threadIdx.x == 0) over = gd->done;
+  __syncthreads();
+  if (over) return;
+  const int j = gd->jc;
+  double v = threadIdx.x < np ? part[threadIdx.x] : 0.0;
+  v = bsum(v, sh);
+  const double hn = sqrt(v);
+  small_pc(w, hn > 0.0 ? 1.0 / hn : 0.0, nv, n, V + (int64_t)(j + 1) * nv, z, pc, pcd);
+  if (blockIdx.x == 0) gm_column(gd, j, hn, flag);
 }
 // cycle start: w = b - A x already in w, partial w.w in part
 __global__ __launch_bounds__(kT) void k_gm_start(const double* part, int np, GmDev* gd, double tol, int m) {
@@ -315,10 +512,11 @@ __global__ __launch_bounds__(kT) void k_gm_start(const double* part, int np, GmD
   gd->conv = beta <= tol ? 1 : 0;
   gd->done = gd->conv;
 }
-__global__ void k_gm_first(double* V, int64_t nv, const double* w, const GmDev* gd) {
+// V_0 = w / |w|; with a pointwise preconditioner also z = M^-1 V_0
+__global__ __launch_bounds__(kT) void k_gm_first(double* V, int64_t nv, int64_t n, const double* w, double* z,
+                                                 const GmDev* gd, int pc, const double* pcd) {
   if (gd->done) return;
-  const double s = gd->hinv;
-  GRID_LOOP(i, nv) V[i] = w[i] * s;
+  small_pc(w, gd->hinv, nv, n, V, z, pc, pcd);
 }
 __global__ __launch_bounds__(kT) void k_resid_part(const double* b, double* w, int64_t n, double* part) {
   __shared__ double sh[4];
@@ -331,14 +529,24 @@ __global__ __launch_bounds__(kT) void k_resid_part(const double* b, double* w, i
   v = bsum(v, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = v;
 }
-// y = R^-1 g over the completed steps (one thread)
-__global__ void k_gm_solve(GmDev* gd) {
-  if (threadIdx.x != 0) return;
-  const int j = gd->j, M1 = gd->m + 1;
-  for (int i = j - 1; i >= 0; --i) {
-    double t = gd->g[i];
-    for (int k = i + 1; k < j; ++k) t -= gd->H[(int64_t)k * M1 + i] * gd->y[k];
-    gd->y[i] = t / gd->H[(int64_t)i * M1 + i];
+// y = R^-1 g over the completed steps: column by column, one lane per row
+// (a thread that walked the rows waited for every entry in turn: 46 us)
+__global__ __launch_bounds__(kGmMax) void k_gm_solve(GmDev* gd) {
+  __shared__ double yk;
+  const int j = gd->j, M1 = gd->m + 1, t = threadIdx.x;
+  double g = t < j ? gd->g[t] : 0.0;
+  const double d = t < j ? gd->H[(int64_t)t * M1 + t] : 1.0;
+  double next = t < j ? gd->H[(int64_t)(j - 1) * M1 + t] : 0.0;
+  for (int k = j - 1; k >= 0; --k) {
+    const double h = next;
+    if (k > 0 && t < k) next = gd->H[(int64_t)(k - 1) * M1 + t];
+    if (t == k) {
+      yk = g / d;
+      gd->y[k] = yk;
+    }
+    __syncthreads();
+    if (t < k) g -= h * yk;
+    __syncthreads();
   }
 }
 // x += M^-1 (sum_k y_k V_k)
@@ -464,6 +672,7 @@ int ensure_stepper(Ctx& c, int m) {
       return CHNS_ENOMEM;
     CHNS_HIP(hipHostMalloc((void**)&S.gd_host, sizeof(GmDev), hipHostMallocDefault));
     CHNS_HIP(hipHostMalloc((void**)&S.red_host, sizeof(double) * 8, hipHostMallocDefault));
+    CHNS_HIP(hipHostMalloc((void**)&S.gm_flag, sizeof(int) * 2, hipHostMallocDefault));
     for (auto& e : S.ev) CHNS_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     // vertical coordinate of every node (energy), zeros
     std::vector<double> y((size_t)n);
@@ -613,29 +822,46 @@ int gmres(Ctx& c, int op, const double* b, double* x, int pc, const double* pcd,
   ApplyOut plain{};
   ApplyOut gated{};
   gated.done = &S.gd->done;
+  const bool mgpc = pc == GPC_SCHUR || pc == GPC_VPMG;
+  const bool small = nv <= kSmallNv;
+  const unsigned gs = (unsigned)std::min<int64_t>((nv + kT - 1) / kT, kSmallBlocks);
+  double* const part2 = S.part + (int64_t)(kGmMax + 1) * kSmallBlocks;  // second dots of the small path
+  // one Arnoldi step; a pointwise preconditioner has already been applied to
+  // V_j by the kernel that formed it
   auto step = [&](hipStream_t st) -> int {
     int e;
-    if (pc == GPC_SCHUR || pc == GPC_VPMG) {
+    if (mgpc) {
       k_gm_copyj<<<blocks_ew(nv), kT, 0, st>>>(S.V, nv, S.pin, S.gd);
       CHNS_HIP(hipGetLastError());
       if ((e = pc == GPC_SCHUR ? ch_schur_apply(c, S.pin, S.z, st) : vp_mg_apply(c, S.pin, S.z, st))) return e;
-    } else {
+    } else if (!small) {
       k_gm_pc<<<blocks_ew(pc == GPC_BLOCK2 ? n : nv), kT, 0, st>>>(S.V, nv, n, S.z, S.gd, pc, pcd);
       CHNS_HIP(hipGetLastError());
     }
     e = launch_apply(c, op, CHNS_FP64, S.z, S.w, st, gated);
     if (e) return e;
+    if (small) {
+      k_gms_dots<<<gs, kT, 0, st>>>(S.V, nv, S.w, S.gd, S.part);
+      k_gms_orth1<<<gs, kT, 0, st>>>(S.V, nv, S.w, S.gd, S.part, part2);
+      k_gms_orth2<<<gs, kT, 0, st>>>(S.V, nv, S.w, S.gd, part2, S.part);
+      k_gms_next<<<gs, kT, 0, st>>>(S.V, nv, n, S.w, S.z, S.gd, pc, pcd, S.part, (int)gs, S.gm_flag);
+      CHNS_HIP(hipGetLastError());
+      return CHNS_OK;
+    }
     for (int pass = 1; pass <= 2; ++pass) {
       k_gm_multidot<<<g, kT, 0, st>>>(S.V, nv, S.w, S.gd, S.part);
       k_gm_fin<<<kGmMax + 1, kT, 0, st>>>(S.part, (int)g, S.gd, pass);
       k_gm_orth<<<g, kT, 0, st>>>(S.V, nv, S.w, S.gd, pass, S.part);
       CHNS_HIP(hipGetLastError());
     }
-    k_gm_givens<<<1, kT, 0, st>>>(S.part, (int)g, S.gd);
+    k_gm_givens<<<1, kT, 0, st>>>(S.part, (int)g, S.gd, S.gm_flag);
     k_gm_scale<<<blocks_ew(nv), kT, 0, st>>>(S.V, nv, S.w, S.gd);
     CHNS_HIP(hipGetLastError());
     return CHNS_OK;
   };
+  // short steps go four to a graph (steps past the end of a cycle test the
+  // done flag and return)
+  const int batch = small && !mgpc && graphs && !c.prof ? 4 : 1;
   hipGraphExec_t exec = nullptr;
   if (graphs && !c.prof) {
     for (auto& ge : S.graphs)
@@ -643,7 +869,8 @@ int gmres(Ctx& c, int op, const double* b, double* x, int pc, const double* pcd,
     if (!exec) {
       hipGraph_t gr = nullptr;
       CHNS_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeRelaxed));
-      int e = step(s);
+      int e = 0;
+      for (int k = 0; k < batch && !e; ++k) e = step(s);
       hipError_t ce = hipStreamEndCapture(s, &gr);
       if (e) return e;
       if (ce != hipSuccess) return hip_fail(ce, "hipStreamEndCapture");
@@ -653,16 +880,15 @@ int gmres(Ctx& c, int op, const double* b, double* x, int pc, const double* pcd,
       S.graphs.push_back({op, pc, (const void*)pcd, exec});
     }
   }
-  const int depth = 4;
   int total = 0;
   while (true) {
     // true residual, first basis vector
     if ((rc = launch_apply(c, op, CHNS_FP64, x, S.w, s, plain))) return rc;
     k_resid_part<<<g, kT, 0, s>>>(b, S.w, nv, S.part);
     k_gm_start<<<1, kT, 0, s>>>(S.part, (int)g, S.gd, tol, m);
-    k_gm_first<<<g, kT, 0, s>>>(S.V, nv, S.w, S.gd);
+    k_gm_first<<<g, kT, 0, s>>>(S.V, nv, n, S.w, S.z, S.gd, small ? pc : GPC_SCHUR, pcd);
     CHNS_HIP(hipGetLastError());
-    CHNS_HIP(hipMemcpyAsync(S.gd_host, S.gd, 64, hipMemcpyDeviceToHost, s));
+    CHNS_HIP(hipMemcpyAsync(S.gd_host, S.gd, offsetof(GmDev, g), hipMemcpyDeviceToHost, s));
     CHNS_HIP(hipStreamSynchronize(s));
     *rel = S.gd_host->beta / bn;
     if (!std::isfinite(*rel)) {
@@ -670,22 +896,24 @@ int gmres(Ctx& c, int op, const double* b, double* x, int pc, const double* pcd,
       return CHNS_ENOCONV;
     }
     if (S.gd_host->conv || total >= max_it) break;
-    // Arnoldi steps until the device flags the end of the cycle
-    for (int it = 0; it < m; ++it) {
+    // Arnoldi steps until the device flags the end of the cycle: one batch
+    // is always queued behind the one whose flag the host waits for
+    for (int it = 0; it < m; it += batch) {
       if (exec) {
         CHNS_HIP(hipGraphLaunch(exec, s));
       } else if ((rc = step(s))) {
         return rc;
       }
-      CHNS_HIP(hipMemcpyAsync(&S.gd_host[0], S.gd, 16, hipMemcpyDeviceToHost, s));
-      if (it % depth == depth - 1 || it == m - 1) {
-        CHNS_HIP(hipStreamSynchronize(s));
-        if (S.gd_host->done) break;
+      const int k = it / batch;
+      CHNS_HIP(hipEventRecord(S.ev[k & 1], s));
+      if (k > 0) {
+        CHNS_HIP(hipEventSynchronize(S.ev[(k - 1) & 1]));
+        if (__atomic_load_n(&S.gm_flag[0], __ATOMIC_ACQUIRE)) break;
       }
     }
     CHNS_HIP(hipStreamSynchronize(s));
-    total += S.gd_host->j;
-    k_gm_solve<<<1, 64, 0, s>>>(S.gd);
+    total += __atomic_load_n(&S.gm_flag[1], __ATOMIC_ACQUIRE);
+    k_gm_solve<<<1, kGmMax, 0, s>>>(S.gd);
     if (pc == GPC_SCHUR || pc == GPC_VPMG) {
       k_gm_combine<<<g, kT, 0, s>>>(S.pin, S.V, nv, S.gd);
       CHNS_HIP(hipGetLastError());
@@ -863,6 +1091,7 @@ void destroy_stepper(Ctx& c) {
     if (e) (void)hipEventDestroy(e);
   if (S.gd_host) (void)hipHostFree(S.gd_host);
   if (S.red_host) (void)hipHostFree(S.red_host);
+  if (S.gm_flag) (void)hipHostFree(S.gm_flag);
   delete c.step;
   c.step = nullptr;
 }
