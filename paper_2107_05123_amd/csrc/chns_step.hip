@@ -318,15 +318,15 @@ __global__ void k_gm_scale(double* V, int64_t nv, const double* w, const GmDev* 
   const double s = gd->hinv;
   GRID_LOOP(i, nv) out[i] = w[i] * s;
 }
-// ---- Arnoldi step of a small system (up to kSmallNv unknowns) in four
+// ---- Arnoldi step of a small system (up to kSmallNv unknowns) in five
 // kernels after the apply: a 2D 64 x 64 step makes about two hundred of them,
 // and at this size a kernel is its launch and one or two chains of dependent
 // loads (3.5 to 9 us), so the one-block reductions between the vector kernels
-// are formed by their consumers, in every block and in one fixed order, and
-// neighbouring passes over the same elements share a kernel: dots, first
-// orthogonalisation with the second dots, second orthogonalisation with the
-// norm, and the new basis vector with the rotations and the next
-// preconditioner application.  Nine kernels an iteration -> four.
+// are formed by their consumers, in every block and in one fixed order: dots
+// and orthogonalisation, twice, then the new basis vector with the rotations
+// and the next preconditioner application.  (The second dots inside the first
+// orthogonalisation saved a kernel but left the basis to 34 blocks: 22 us for
+// dots, orthogonalisation and dots against 18 us.)
 constexpr int kSmallNv = 65536;
 constexpr int kSmallBlocks = 128;
 constexpr int kSmallEpt = kSmallNv / (kSmallBlocks * kT);  // elements per thread
@@ -349,28 +349,6 @@ __device__ __forceinline__ double wsum16(double (&a)[16], int lane) {
   t += __shfl_xor(t, 16, 64);
   t += __shfl_xor(t, 32, 64);
   return t;
-}
-// part[block][k] = sum over the block's elements of V_k t, k <= j
-template <int EPT>
-__device__ __forceinline__ void small_dots(const double* V, int64_t nv, int j, const double (&t)[EPT],
-                                           const int (&idx)[EPT], double* part) {
-  __shared__ double red[4][kGmMax + 16];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int k0 = 0; k0 <= j; k0 += 16) {
-    double a[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      a[q] = 0.0;
-#pragma unroll
-      for (int e = 0; e < EPT; ++e)
-        if (k0 + q <= j && idx[e] < nv) a[q] += V[(int64_t)(k0 + q) * nv + idx[e]] * t[e];
-    }
-    const double s = wsum16(a, lane);
-    if (lane < 16) red[w][k0 + (int)(__brev((unsigned)lane) >> 28)] = s;
-  }
-  __syncthreads();
-  for (int k = threadIdx.x; k <= j; k += kT)
-    part[(int64_t)blockIdx.x * (kGmMax + 1) + k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
 }
 // hs[k] = sum over np blocks of part[block][k], k <= j
 __device__ __forceinline__ void small_total(const double* part, int np, int j, double* hs) {
@@ -405,41 +383,46 @@ __device__ __forceinline__ void small_orth(const double* V, int64_t nv, int j, c
     for (int k = 0; k <= j; ++k) t[e] -= hs[k] * V[(int64_t)k * nv + idx[e]];
   }
 }
+// part[block][k] = sum over the block's elements of V_k w, k <= j: sixteen k
+// per block row, so that a long basis is read by many CUs at once
 __global__ __launch_bounds__(kT) void k_gms_dots(const double* V, int64_t nv, const double* w, const GmDev* gd,
                                                  double* part) {
+  __shared__ double red[4][16];
   if (gd->done) return;
+  const int j = gd->j, k0 = blockIdx.y * 16;
+  if (k0 > j) return;
   int idx[kSmallEpt];
-  double t[kSmallEpt];
   small_index(idx);
+  double a[16];
 #pragma unroll
-  for (int e = 0; e < kSmallEpt; ++e) t[e] = idx[e] < nv ? w[idx[e]] : 0.0;
-  small_dots(V, nv, gd->j, t, idx, part);
-}
-__global__ __launch_bounds__(kT) void k_gms_orth1(const double* V, int64_t nv, double* w, GmDev* gd,
-                                                  const double* part, double* part2) {
-  __shared__ double hs[kGmMax];
-  if (gd->done) return;
-  const int j = gd->j;
-  small_total(part, gridDim.x, j, hs);
-  if (blockIdx.x == 0 && threadIdx.x <= j) gd->h1[threadIdx.x] = hs[threadIdx.x];
-  int idx[kSmallEpt];
-  double t[kSmallEpt];
-  small_index(idx);
-  small_orth(V, nv, j, w, hs, idx, t);
+  for (int q = 0; q < 16; ++q) a[q] = 0.0;
 #pragma unroll
-  for (int e = 0; e < kSmallEpt; ++e)
-    if (idx[e] < nv) w[idx[e]] = t[e];
-  small_dots(V, nv, j, t, idx, part2);
+  for (int e = 0; e < kSmallEpt; ++e) {
+    if (idx[e] >= nv) continue;
+    const double t = w[idx[e]];
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      if (k0 + q <= j) a[q] += V[(int64_t)(k0 + q) * nv + idx[e]] * t;
+  }
+  const int lane = threadIdx.x & 63;
+  const double s = wsum16(a, lane);
+  if (lane < 16) red[threadIdx.x >> 6][__brev((unsigned)lane) >> 28] = s;
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k < 16 && k0 + k <= j)
+    part[(int64_t)blockIdx.x * (kGmMax + 1) + k0 + k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
 }
-__global__ __launch_bounds__(kT) void k_gms_orth2(const double* V, int64_t nv, double* w, GmDev* gd,
-                                                  const double* part2, double* part) {
+// w -= sum_k h_k V_k with h_k the totals of the dots; the first block keeps
+// them for the Hessenberg column, the second pass leaves partials of w.w
+__global__ __launch_bounds__(kT) void k_gms_orth(const double* V, int64_t nv, double* w, GmDev* gd, int which,
+                                                 const double* part, double* part_ww) {
   __shared__ double hs[kGmMax];
   __shared__ double sh[4];
   if (gd->done) return;
   const int j = gd->j;
-  small_total(part2, gridDim.x, j, hs);
+  small_total(part, gridDim.x, j, hs);
   if (blockIdx.x == 0) {
-    if (threadIdx.x <= j) gd->h2[threadIdx.x] = hs[threadIdx.x];
+    if (threadIdx.x <= j) (which == 1 ? gd->h1 : gd->h2)[threadIdx.x] = hs[threadIdx.x];
     if (threadIdx.x == 0) gd->jc = j;
   }
   int idx[kSmallEpt];
@@ -452,8 +435,9 @@ __global__ __launch_bounds__(kT) void k_gms_orth2(const double* V, int64_t nv, d
       w[idx[e]] = t[e];
       ww += t[e] * t[e];
     }
+  if (which == 1) return;
   ww = bsum(ww, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = ww;
+  if (threadIdx.x == 0) part_ww[blockIdx.x] = ww;
 }
 // z = M^-1 v of a pointwise preconditioner
 __device__ __forceinline__ void small_pc(const double* v, double s, int64_t nv, int64_t n, double* out, double* z,
@@ -825,7 +809,7 @@ int gmres(Ctx& c, int op, const double* b, double* x, int pc, const double* pcd,
   const bool mgpc = pc == GPC_SCHUR || pc == GPC_VPMG;
   const bool small = nv <= kSmallNv;
   const unsigned gs = (unsigned)std::min<int64_t>((nv + kT - 1) / kT, kSmallBlocks);
-  double* const part2 = S.part + (int64_t)(kGmMax + 1) * kSmallBlocks;  // second dots of the small path
+  double* const part_ww = S.part + (int64_t)(kGmMax + 1) * kSmallBlocks;  // behind the dots of the small path
   // one Arnoldi step; a pointwise preconditioner has already been applied to
   // V_j by the kernel that formed it
   auto step = [&](hipStream_t st) -> int {
@@ -841,10 +825,11 @@ int gmres(Ctx& c, int op, const double* b, double* x, int pc, const double* pcd,
     e = launch_apply(c, op, CHNS_FP64, S.z, S.w, st, gated);
     if (e) return e;
     if (small) {
-      k_gms_dots<<<gs, kT, 0, st>>>(S.V, nv, S.w, S.gd, S.part);
-      k_gms_orth1<<<gs, kT, 0, st>>>(S.V, nv, S.w, S.gd, S.part, part2);
-      k_gms_orth2<<<gs, kT, 0, st>>>(S.V, nv, S.w, S.gd, part2, S.part);
-      k_gms_next<<<gs, kT, 0, st>>>(S.V, nv, n, S.w, S.z, S.gd, pc, pcd, S.part, (int)gs, S.gm_flag);
+      for (int pass = 1; pass <= 2; ++pass) {
+        k_gms_dots<<<dim3(gs, (kGmMax + 15) / 16), kT, 0, st>>>(S.V, nv, S.w, S.gd, S.part);
+        k_gms_orth<<<gs, kT, 0, st>>>(S.V, nv, S.w, S.gd, pass, S.part, part_ww);
+      }
+      k_gms_next<<<gs, kT, 0, st>>>(S.V, nv, n, S.w, S.z, S.gd, pc, pcd, part_ww, (int)gs, S.gm_flag);
       CHNS_HIP(hipGetLastError());
       return CHNS_OK;
     }
