@@ -30,8 +30,6 @@ namespace {
 // host-side stand-in; kernels get the device address from scratch_address().
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
-constexpr double kGauss = 0.57735026918962576451;  // 1/sqrt(3)
-
 // ------------------------------------------------------------ arithmetic
 __device__ __forceinline__ double rcp_t(double r) {
   // hardware estimate refined by two Newton steps (error well below 1e-15)
@@ -62,16 +60,25 @@ __device__ __forceinline__ float clamp_t(float v, float lim) { return __builtin_
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
-// 1D two-node / two-Gauss-point transform, scaled by 2: (a, b) nodal values
-// -> values at xi = -1/sqrt3, +1/sqrt3.  The 2x2 matrix is symmetric, so the
-// same transform also applies the transpose.
+// 1D two-node / two-Gauss-point transform, scaled by 1/w: (a, b) nodal values
+// -> (a + c b, c a + b) = values at xi = -1/sqrt3, +1/sqrt3 over w, with
+// w = (1 + 1/sqrt3)/2 and c = 2 - sqrt3: two multiply-adds (sum, difference
+// and one multiply-add for each point took four operations; the transforms
+// are half of the momentum leaf's FP64 work).  The matrix is symmetric, so the
+// same transform also applies the transpose.  The powers of w are folded into
+// the forms' constants.
 template <typename T>
 __device__ __forceinline__ void pair_tf(T& a, T& b) {
-  T t = a + b;
-  T u = b - a;
-  a = fma_t(T(-kGauss), u, t);
-  b = fma_t(T(kGauss), u, t);
+  T u, v;
+  march::tf(a, b, u, v);
+  a = u;
+  b = v;
 }
+// w^n
+template <int N>
+constexpr double kWp = march::kW * kWp<N - 1>;
+template <>
+inline constexpr double kWp<0> = 1.0;
 template <int N, int BIT, typename T>
 __device__ __forceinline__ void stage(T* v) {
 #pragma unroll
@@ -88,10 +95,10 @@ __device__ __forceinline__ void all_stages(T* v) {
 __host__ __device__ constexpr int insert0(int r, int d) { return (r & ((1 << d) - 1)) | ((r >> d) << (d + 1)); }
 
 // --------------------------------------------------------- element operators
-// Folded constants: with values scaled by 2^d through the stages, the Gauss
-// weights (1), det J = (h/2)^d and the (2/h)^2 of two gradients collapse into
-// per-level powers of two (exact), so c_q = 1/rho(phi*_q) costs one fma, one
-// clamp and one reciprocal per Gauss point.
+// Folded constants: with values scaled by w^-d through the stages, the Gauss
+// weights (1), det J = (h/2)^d, the (2/h)^2 of two gradients and the powers of
+// w collapse into per-level constants, so c_q = 1/rho(phi*_q) costs one fma,
+// one clamp and one reciprocal per Gauss point.
 
 // Pressure Poisson: y_a = sum_q detJ (2/h)^2 c_q gradN_a . grad x,
 // c_q = 1/rho(clamp(phi_q)) (Def. 2, VMS pressure Poisson; pull back remark).
@@ -104,7 +111,7 @@ __device__ __forceinline__ void elem_pp_coef(const T* ph, T A, T Bc, T* c) {
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
     // coefficient 1 / (A phi + B) (pressure) or A phi + B (viscosity)
-    const T lin = fma_t(A, clamp_t(c[i], T(NC)), Bc);
+    const T lin = fma_t(A, clamp_t(c[i], T(1.0 / kWp<DIM>)), Bc);
     c[i] = RCP ? rcp_t(lin) : lin;
   }
 }
@@ -155,7 +162,7 @@ __device__ __forceinline__ void elem_mass_coef(const T* ph, T A, T Bc, T* r) {
     for (int i = 0; i < NC; ++i) r[i] = ph[i];
     all_stages<DIM>(r);
 #pragma unroll
-    for (int i = 0; i < NC; ++i) r[i] = fma_t(A, clamp_t(r[i], T(NC)), Bc);
+    for (int i = 0; i < NC; ++i) r[i] = fma_t(A, clamp_t(r[i], T(1.0 / kWp<DIM>)), Bc);
   } else {
 #pragma unroll
     for (int i = 0; i < NC; ++i) r[i] = Bc;
@@ -482,9 +489,9 @@ template <int DIM, typename T, class CV>
 __device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (*y)[1 << DIM]) {
   constexpr int NC = 1 << DIM, H = NC / 2;
   const double h = ldexp(1.0, -lev);
-  // (2^d scaling of each transform) x (2^d of the transpose) folded into w
-  const T w = T(ldexp(1.0, -(lev + 1) * DIM - 2 * DIM));
-  const T inv2d = T(ldexp(1.0, -DIM));
+  // the w^d of a transform and of its transpose folded into the weight
+  const T w = T(ldexp(kWp<2 * DIM>, -(lev + 1) * DIM));
+  const T wd = T(kWp<DIM>);
   // stiffness parts, corner form
   {
     T xp[NC], xm[NC];
@@ -514,7 +521,7 @@ __device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (
       y[0][a] = kmu * km;
       y[1][a] = kphi * kp;
     }
-    // mass parts at the Gauss points (values scaled by 2^d)
+    // mass parts at the Gauss points (values scaled by w^-d)
     all_stages<DIM>(xp);
     all_stages<DIM>(xm);
     T pt[NC];
@@ -525,7 +532,7 @@ __device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (
     const T idt = T(1.0 / P.dt);
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      const T p = pt[q] * inv2d;
+      const T p = pt[q] * wd;
       const T d2 = T(3) * p * p - T(1);
       fa[q] = w * idt * xp[q];
       fb[q] = w * T(0.5) * (d2 * xp[q] - xm[q]);
@@ -539,7 +546,7 @@ __device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (
     }
     // advection -1/2 (grad q, u~ dphi): flux F_d = -1/2 det J u~_d dphi at
     // each Gauss point, then the transposed gradient (constant along d)
-    const T wa = T(-0.5 * ldexp(1.0, -(lev + 1) * DIM) * ldexp(1.0, lev) * ldexp(1.0, -2 * DIM - (DIM - 1)));
+    const T wa = T(-0.5 * ldexp(kWp<3 * DIM - 1>, -(lev + 1) * DIM + lev));
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
       T u[NC];
@@ -572,10 +579,14 @@ __device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (
 //   Galerkin part  N_a rho~ (v/dt + b.grad v) + k grad N_a . grad v,
 //   stabilisation  (b.grad N_a) tau_m R_lin(v).
 // Sum-factorised: every field's values at the Gauss points come from the
-// two-point transforms (scaled by S = 2^d), its gradient along d from the
+// two-point transforms (w^-d times the value), its gradient along d from the
 // differences along d carried through the transforms of the other
 // directions (constant along d, so shared by the two Gauss points of a
-// column); the test functions are applied by the same transforms
+// column).  In units of the transformed values a gradient is gamma times the
+// transformed difference, gamma = (2/h)/(2 w), and the same factor stands in
+// front of a gradient test function, so b and k are stored as gamma b and
+// gamma^2 k and the weight det J w^2d goes into rho, k and grad eta~;
+// the test functions are applied by the same transforms
 // transposed.  The coefficients are formed once per Gauss point (the phase
 // field clamped, tau_m, b scaled by 2/h, grad phi~ per column with the
 // pull-back mask per point), then each component is transformed, combined
@@ -585,20 +596,20 @@ template <int DIM, typename T, class CV, class OUT>
 __device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, const OUT& out) {
   constexpr int NC = 1 << DIM, H = NC / 2;
   const PhaseT<T> ph = phase_of<T>(P);
-  // powers of two (2/h = 2^e1, det J = 2^-d e1, S = 2^d) are applied with
-  // ldexp: exact, and no per-level constants held in registers
+  // powers of two (2/h = 2^e1, det J = 2^-d e1) are applied with ldexp: exact,
+  // and no per-level constants held in registers
   const int e1 = lev + 1;
-  const double iS = ldexp(1.0, -DIM);  // 1/S
+  constexpr double wd = kWp<DIM>, w2d = kWp<2 * DIM>, g1 = 1.0 / (2.0 * march::kW);  // gamma / (2/h)
   const T idt = T(1.0 / P.dt);
-  // k (2/h)^2 = (ea s + eb) / (2 Re) (2/h)^2; grad eta~ / (2 Re) (2/h) per
-  // transformed column; J / (2 Pe) per transformed column
-  const T kea = T(P.gam / (2.0 * P.Re)), keb = T(ph.eb / (2.0 * P.Re));
-  const T cgp = T(P.gam / (2.0 * P.Re) * iS);
-  const T cJ = T(P.cJ * iS / (2.0 * P.Pe));
+  // gamma^2 k, gamma^2 w^d gam/(2 Re) (grad eta~ of a transformed column, one
+  // gamma its own and one of grad v) and gamma J / (2 Pe), without their 2/h
+  const T kea = T(P.gam / (2.0 * P.Re) * (g1 * g1 * w2d)), keb = T(ph.eb / (2.0 * P.Re) * (g1 * g1 * w2d));
+  const T cgp = T(P.gam / (2.0 * P.Re) * (wd * g1 * g1 * w2d));
+  const T cJ = T(P.cJ * (wd * g1 * g1) / (2.0 * P.Pe));
   const T tau_c = T(4.0 / (P.dt * P.dt));
   const T visc_c = T(P.C_I * DIM);
   const T ire = T(1.0 / P.Re);
-  const T iSt = T(iS);
+  const T iSt = T(wd);
 
   // ---- coefficients at the Gauss points
   T sc[NC], tau[NC], bs[DIM][NC], gp[DIM][H];
@@ -664,20 +675,21 @@ __device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, cons
       for (int q = 0; q < NC; ++q) {
         const int r = (q & ((1 << d) - 1)) | ((q >> (d + 1)) << d);
         const T uh = u[q] * iSt;
-        const T j2 = J[d][r];  // J / (2 Pe)
+        const T j2 = J[d][r];  // gamma J / (2 Pe) over 2/h
         uu[q] = fma_t(uh, uh, uu[q]);
         uJ[q] = fma_t(uh, j2, uJ[q]);
-        bs[d][q] = ldexp(fma_t(j2, irho[q], T(0.5) * uh), e1);
+        bs[d][q] = ldexp(fma_t(j2, irho[q], T(0.5 * g1) * uh), e1);
       }
     }
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       const T r = (ph.ea * sc[q] + ph.eb) * irho[q] * ire;
       // u^.J / (Pe rho~) = 2 u^.(J / (2 Pe)) / rho~
-      tau[q] = rsqrt_t(tau_c + ldexp(fma_t(T(2) * uJ[q], irho[q], uu[q]), 2 * e1) + ldexp(visc_c * r * r, 4 * e1));
+      tau[q] = rsqrt_t(tau_c + ldexp(fma_t(T(2.0 / g1) * uJ[q], irho[q], uu[q]), 2 * e1) + ldexp(visc_c * r * r, 4 * e1));
     }
   }
-  // ---- the components in turn
+  // ---- the components in turn (rho with the weight w^2d)
+  const T rwa = T(ph.ra * T(w2d)), rwb = T(ph.rb * T(w2d));
 #pragma unroll
   for (int f = 0; f < DIM; ++f) {
     asm volatile("" ::: "memory");
@@ -698,7 +710,7 @@ __device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, cons
     all_stages<DIM>(v);
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      const T rho = ph.ra * sc[q] + ph.rb;
+      const T rho = rwa * sc[q] + rwb;
       const T kg = ldexp(fma_t(kea, sc[q], keb), 2 * e1);
       T Gh = idt * v[q], gg = T(0);
 #pragma unroll
@@ -729,7 +741,7 @@ __device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, cons
       }
     }
 #pragma unroll
-    for (int a = 0; a < NC; ++a) v[a] = ldexp(v[a], -(e1 + 2) * DIM);  // det J / S^2
+    for (int a = 0; a < NC; ++a) v[a] = ldexp(v[a], -e1 * DIM);  // det J
     out(f, v);
   }
 }
@@ -763,33 +775,34 @@ struct OpConst {
 };
 template <int DIM, typename T, int OP>
 __device__ __forceinline__ OpConst<T> op_const(const BrickArgs<T>& a, int lev) {
-  // per-level folded constants (powers of two are exact); FP32 fields carry
-  // 1 + phi, so rho = (beta - alpha) + alpha (1 + phi)
+  // FP32 fields carry 1 + phi, so rho = (beta - alpha) + alpha (1 + phi)
   const double beta0 = sizeof(T) == 8 ? a.beta : a.beta - a.alpha;
   OpConst<T> o;
-  if constexpr (OP == K_PPS) o.Ms = T(a.shift * ldexp(1.0, -(lev + 1) * DIM - 2 * DIM));
+  // mass: det J w^2d; stiffness: (h/2)^(d-2) / 4 w^2(d-1); phi: w^d
+  const double mass = ldexp(kWp<2 * DIM>, -(lev + 1) * DIM);
+  const double F = ldexp(kWp<2 * (DIM - 1)> / 4.0, -(lev + 1) * (DIM - 2));
+  constexpr double wd = kWp<DIM>;
+  if constexpr (OP == K_PPS) o.Ms = T(a.shift * mass);
   if constexpr (OP == K_VPS) {
     // viscosity eta/(2 Re) = (gam phi + xi)/(2 Re) on the stiffness (folded
     // like the pressure coefficient, without the reciprocal) and rho/dt on
     // the mass
-    const int es = (lev + 1) * (DIM - 2) + 2 * DIM, em = -(lev + 1) * DIM - 2 * DIM;
     const double g2 = a.phys.gam / (2.0 * a.phys.Re), x2 = a.phys.xi / (2.0 * a.phys.Re);
-    o.A = T(ldexp(g2, -es - DIM));
-    o.Bc = T(ldexp(sizeof(T) == 8 ? x2 : x2 - g2, -es));
-    o.Am = T(ldexp(a.alpha / a.phys.dt, em - DIM));
-    o.Bm = T(ldexp(beta0 / a.phys.dt, em));
+    o.A = T(g2 * F * wd);
+    o.Bc = T((sizeof(T) == 8 ? x2 : x2 - g2) * F);
+    o.Am = T(a.alpha / a.phys.dt * mass * wd);
+    o.Bm = T(beta0 / a.phys.dt * mass);
   }
   if constexpr (OP == K_PP || OP == K_PPS) {
-    // c~ = detJ (2/h)^2 / 4^d / rho = 1 / (rho / K); K = 2^{-(lev+1)(d-2) - 2d}
-    const int e = (lev + 1) * (DIM - 2) + 2 * DIM;
-    o.A = T(ldexp(a.alpha, e - DIM));
-    o.Bc = T(ldexp(beta0, e));
+    // c~ = F / rho = 1 / (rho / F)
+    const double f = ldexp(4.0 / kWp<2 * (DIM - 1)>, (lev + 1) * (DIM - 2));
+    o.A = T(a.alpha * f * wd);
+    o.Bc = T(beta0 * f);
   } else if constexpr (OP == K_MASS) {
-    o.Bc = T(ldexp(1.0, -(lev + 1) * DIM - 2 * DIM));
+    o.Bc = T(mass);
   } else if constexpr (OP == K_MASS_RHO) {
-    const int e = -(lev + 1) * DIM - 2 * DIM;
-    o.A = T(ldexp(a.alpha, e - DIM));
-    o.Bc = T(ldexp(beta0, e));
+    o.A = T(a.alpha * mass * wd);
+    o.Bc = T(beta0 * mass);
   }
   return o;
 }
