@@ -212,6 +212,20 @@ CHNS_TRAITS(K_DIAG, 1, 1, 1, false, 0)  // diagonal of the scalar operators (the
 
 constexpr int kMaxCoef = kMaxCoefFields;
 
+// Constants of the Cahn-Hilliard Jacobian and the momentum form, evaluated on
+// the host: kernel arguments sit in scalar registers, where the divisions that
+// form them would leave 28 vector registers occupied through the march.
+template <typename T>
+struct FormConst {
+  T idt;                     // 1 / dt
+  T kphi, kmu;               // Jacobian: stiffness of phi and mu over h^(d-2)
+  T ra, rb, rwa, rwb;        // momentum: rho = ra s + rb, the same times w^2d
+  T kea, keb, cgp, cJ;       // gamma^2 k, grad eta~, gamma J / (2 Pe) (el_vp)
+  T tau_c, va, vb, vc;       // 4 / dt^2, eta / Re = va s + vb, C_I d
+};
+template <int DIM, typename T>
+FormConst<T> form_const(const Phys& P);
+
 template <typename T>
 struct BrickArgs {
   const int32_t* table;
@@ -239,6 +253,7 @@ struct BrickArgs {
   T sm_w;
   double shift;  // K_PPS: mass shift
   int diag_of;   // K_DIAG: the operator's form
+  FormConst<T> fc;  // K_CH_JAC, K_VP
   // structured (uniform, lexicographically numbered) meshes: node indices are
   // computed from the brick anchor instead of read from the table
   const int32_t* anchor;  // 3 per brick, integer node coordinates
@@ -456,23 +471,32 @@ __device__ __forceinline__ void el_energy(const double (*c)[1 << DIM], const Phy
 //
 // Phase-field storage: FP64 fields hold phi, FP32 fields hold 1 + phi (so
 // that rho = (beta - alpha) + alpha (1 + phi) keeps its relative accuracy
-// near phi = -1 at large density ratios); PhaseT gives the pull-back range
-// and the mixture laws in the stored variable.
-template <typename T>
-struct PhaseT {
-  T lo, hi;          // range of the stored variable (phi* in [-1, 1])
-  T ra, rb, ea, eb;  // rho = ra s + rb, eta = ea s + eb with s the stored value
-};
-template <typename T>
-__device__ __forceinline__ PhaseT<T> phase_of(const Phys& P) {
-  PhaseT<T> f;
+// near phi = -1 at large density ratios); the pull-back range and the mixture
+// laws rho = ra s + rb, eta = ea s + eb are in the stored variable s.
+template <int DIM, typename T>
+FormConst<T> form_const(const Phys& P) {
+  constexpr double wd = kWp<DIM>, w2d = kWp<2 * DIM>, g1 = 1.0 / (2.0 * march::kW);  // gamma / (2/h)
   const bool shifted = sizeof(T) == 4;
-  f.lo = shifted ? T(0) : T(-1);
-  f.hi = shifted ? T(2) : T(1);
+  const double rb = shifted ? P.beta - P.alpha : P.beta, eb = shifted ? P.xi - P.gam : P.xi;
+  const double st = DIM == 3 ? 1.0 / 12.0 : 1.0 / 6.0;
+  FormConst<T> f;
+  f.idt = T(1.0 / P.dt);
+  f.kphi = T(st * P.Cn * P.Cn * 0.5);
+  f.kmu = T(st / (2.0 * P.Pe * P.Cn));
   f.ra = T(P.alpha);
-  f.rb = T(shifted ? P.beta - P.alpha : P.beta);
-  f.ea = T(P.gam);
-  f.eb = T(shifted ? P.xi - P.gam : P.xi);
+  f.rb = T(rb);
+  f.rwa = T(P.alpha * w2d);
+  f.rwb = T(rb * w2d);
+  // gamma^2 k, gamma^2 w^d gam/(2 Re) (grad eta~ of a transformed column, one
+  // gamma its own and one of grad v) and gamma J / (2 Pe), without their 2/h
+  f.kea = T(P.gam / (2.0 * P.Re) * (g1 * g1 * w2d));
+  f.keb = T(eb / (2.0 * P.Re) * (g1 * g1 * w2d));
+  f.cgp = T(P.gam / (2.0 * P.Re) * (wd * g1 * g1 * w2d));
+  f.cJ = T(P.cJ * (wd * g1 * g1) / (2.0 * P.Pe));
+  f.tau_c = T(4.0 / (P.dt * P.dt));
+  f.va = T(P.gam / P.Re);
+  f.vb = T(eb / P.Re);
+  f.vc = T(P.C_I * DIM);
   return f;
 }
 
@@ -486,9 +510,8 @@ __device__ __forceinline__ PhaseT<T> phase_of(const Phys& P) {
 // - 2 opposite corner)/6), the advection flux through the transposed
 // gradient.  cv(f, a): f = 0 dphi, 1 dmu, 2 phi~, 3.. u~.
 template <int DIM, typename T, class CV>
-__device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (*y)[1 << DIM]) {
+__device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int lev, T (*y)[1 << DIM]) {
   constexpr int NC = 1 << DIM, H = NC / 2;
-  const double h = ldexp(1.0, -lev);
   // the w^d of a transform and of its transpose folded into the weight
   const T w = T(ldexp(kWp<2 * DIM>, -(lev + 1) * DIM));
   const T wd = T(kWp<DIM>);
@@ -500,8 +523,7 @@ __device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (
       xp[a] = cv(0, a);
       xm[a] = cv(1, a);
     }
-    const T kphi = T((DIM == 3 ? h / 12.0 : 1.0 / 6.0) * P.Cn * P.Cn * 0.5);
-    const T kmu = T((DIM == 3 ? h / 12.0 : 1.0 / 6.0) / (2.0 * P.Pe * P.Cn));
+    const T kphi = ldexp(K.kphi, -lev * (DIM - 2)), kmu = ldexp(K.kmu, -lev * (DIM - 2));
     T sp = T(0), sm = T(0);
 #pragma unroll
     for (int a = 0; a < NC; ++a) {
@@ -529,12 +551,12 @@ __device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (
     for (int a = 0; a < NC; ++a) pt[a] = cv(2, a);
     all_stages<DIM>(pt);
     T fa[NC], fb[NC];
-    const T idt = T(1.0 / P.dt);
+    const T wi = w * K.idt;
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       const T p = pt[q] * wd;
       const T d2 = T(3) * p * p - T(1);
-      fa[q] = w * idt * xp[q];
+      fa[q] = wi * xp[q];
       fb[q] = w * T(0.5) * (d2 * xp[q] - xm[q]);
     }
     all_stages<DIM>(fa);
@@ -593,23 +615,15 @@ __device__ __forceinline__ void el_chj(const CV& cv, const Phys& P, int lev, T (
 // and handed to out(f, y) in turn.  cv(f, a): f < DIM the velocity
 // components, then phi~ (stored as in PhaseT), mu~, u^.
 template <int DIM, typename T, class CV, class OUT>
-__device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, const OUT& out) {
+__device__ __forceinline__ void el_vp(const CV& cv, const FormConst<T>& K, int lev, const OUT& out) {
   constexpr int NC = 1 << DIM, H = NC / 2;
-  const PhaseT<T> ph = phase_of<T>(P);
+  // range of the stored phase field (phi* in [-1, 1])
+  constexpr T lo_s = sizeof(T) == 4 ? T(0) : T(-1), hi_s = sizeof(T) == 4 ? T(2) : T(1);
   // powers of two (2/h = 2^e1, det J = 2^-d e1) are applied with ldexp: exact,
   // and no per-level constants held in registers
   const int e1 = lev + 1;
-  constexpr double wd = kWp<DIM>, w2d = kWp<2 * DIM>, g1 = 1.0 / (2.0 * march::kW);  // gamma / (2/h)
-  const T idt = T(1.0 / P.dt);
-  // gamma^2 k, gamma^2 w^d gam/(2 Re) (grad eta~ of a transformed column, one
-  // gamma its own and one of grad v) and gamma J / (2 Pe), without their 2/h
-  const T kea = T(P.gam / (2.0 * P.Re) * (g1 * g1 * w2d)), keb = T(ph.eb / (2.0 * P.Re) * (g1 * g1 * w2d));
-  const T cgp = T(P.gam / (2.0 * P.Re) * (wd * g1 * g1 * w2d));
-  const T cJ = T(P.cJ * (wd * g1 * g1) / (2.0 * P.Pe));
-  const T tau_c = T(4.0 / (P.dt * P.dt));
-  const T visc_c = T(P.C_I * DIM);
-  const T ire = T(1.0 / P.Re);
-  const T iSt = T(wd);
+  constexpr double g1 = 1.0 / (2.0 * march::kW);  // gamma / (2/h)
+  const T iSt = T(kWp<DIM>);
 
   // ---- coefficients at the Gauss points
   T sc[NC], tau[NC], bs[DIM][NC], gp[DIM][H];
@@ -628,14 +642,14 @@ __device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, cons
       stage<H, 1>(gp[d]);
       if constexpr (H > 2) stage<H, 2>(gp[d]);
 #pragma unroll
-      for (int r = 0; r < H; ++r) gp[d][r] = ldexp(gp[d][r] * cgp, 2 * e1);
+      for (int r = 0; r < H; ++r) gp[d][r] = ldexp(gp[d][r] * K.cgp, 2 * e1);
     }
     all_stages<DIM>(v);
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       const T s = v[q] * iSt;
-      sc[q] = fmin(fmax(s, ph.lo), ph.hi);
-      if (s > ph.lo && s < ph.hi) inside |= 1u << q;
+      sc[q] = fmin(fmax(s, lo_s), hi_s);
+      if (s > lo_s && s < hi_s) inside |= 1u << q;
     }
   }
   asm volatile("" ::: "memory");
@@ -655,13 +669,13 @@ __device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, cons
         stage<H, 1>(J[d]);
         if constexpr (H > 2) stage<H, 2>(J[d]);
 #pragma unroll
-        for (int r = 0; r < H; ++r) J[d][r] = ldexp(J[d][r] * cJ, e1);
+        for (int r = 0; r < H; ++r) J[d][r] = ldexp(J[d][r] * K.cJ, e1);
       }
     }
     T irho[NC], uu[NC], uJ[NC];
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      irho[q] = rcp_t(ph.ra * sc[q] + ph.rb);
+      irho[q] = rcp_t(fma_t(K.ra, sc[q], K.rb));
       uu[q] = uJ[q] = T(0);
     }
 #pragma unroll
@@ -683,13 +697,12 @@ __device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, cons
     }
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      const T r = (ph.ea * sc[q] + ph.eb) * irho[q] * ire;
+      const T r = fma_t(K.va, sc[q], K.vb) * irho[q];
       // u^.J / (Pe rho~) = 2 u^.(J / (2 Pe)) / rho~
-      tau[q] = rsqrt_t(tau_c + ldexp(fma_t(T(2.0 / g1) * uJ[q], irho[q], uu[q]), 2 * e1) + ldexp(visc_c * r * r, 4 * e1));
+      tau[q] = rsqrt_t(K.tau_c + ldexp(fma_t(T(2.0 / g1) * uJ[q], irho[q], uu[q]), 2 * e1) + ldexp(K.vc * r * r, 4 * e1));
     }
   }
   // ---- the components in turn (rho with the weight w^2d)
-  const T rwa = T(ph.ra * T(w2d)), rwb = T(ph.rb * T(w2d));
 #pragma unroll
   for (int f = 0; f < DIM; ++f) {
     asm volatile("" ::: "memory");
@@ -710,9 +723,9 @@ __device__ __forceinline__ void el_vp(const CV& cv, const Phys& P, int lev, cons
     all_stages<DIM>(v);
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      const T rho = rwa * sc[q] + rwb;
-      const T kg = ldexp(fma_t(kea, sc[q], keb), 2 * e1);
-      T Gh = idt * v[q], gg = T(0);
+      const T rho = fma_t(K.rwa, sc[q], K.rwb);
+      const T kg = ldexp(fma_t(K.kea, sc[q], K.keb), 2 * e1);
+      T Gh = K.idt * v[q], gg = T(0);
 #pragma unroll
       for (int d = 0; d < DIM; ++d) {
         const int r = (q & ((1 << d) - 1)) | ((q >> (d + 1)) << d);
@@ -914,9 +927,9 @@ __device__ __forceinline__ void leaf_form(const BrickArgs<T>& a, const OpConst<T
   if constexpr (OP == K_DIAG) {
     leaf_diag<DIM, T>(a, lev, xc[0], cc[0], ye[0]);
   } else if constexpr (OP == K_CH_JAC) {
-    el_chj<DIM, T>(cv, a.phys, lev, ye);
+    el_chj<DIM, T>(cv, a.fc, lev, ye);
   } else if constexpr (OP == K_VP) {
-    el_vp<DIM, T>(cv, a.phys, lev, out);
+    el_vp<DIM, T>(cv, a.fc, lev, out);
   } else if constexpr (OP == K_PP || OP == K_PPS) {
     elem_pp<DIM, T>(xc[0], cc[0], oc.A, oc.Bc, ye[0]);
     if constexpr (OP == K_PPS) {
@@ -1537,10 +1550,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
   __shared__ ShmOf<DIM, B, T, OP> sm;
   brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT>(a, sm, blockIdx.x, gridDim.x);
 }
-// the FP64 3D Cahn-Hilliard Jacobian on structured 8^3 bricks: its LDS
-// admits three waves per SIMD, which at 128^3 leaves a third of the bricks
-// to a second, sparse round; held to two waves it runs two full rounds
-// (0.095 -> 0.090 ms; equal at 256^3; on adaptive meshes three are faster)
+// two FP64 3D forms on 8^3 bricks.  The Cahn-Hilliard Jacobian on structured
+// bricks: its LDS admits three waves per SIMD, which at 128^3 leaves a third
+// of the bricks to a second, sparse round; held to two waves it runs two full
+// rounds (0.095 -> 0.090 ms; equal at 256^3; on adaptive meshes three are
+// faster).  The momentum form: a chain of dependent FMAs and reciprocals
+// bounds it, and left alone the compiler takes more than 256 registers and
+// one wave per SIMD; held to two it spills 12 bytes a lane on structured
+// bricks and 80 on table bricks and still gains, 192 -> 164 us at 128^3 and
+// 461 -> 426 us on the 5-9 octree
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_brick_o2(BrickArgs<T> a) {
   __shared__ ShmOf<DIM, B, T, OP> sm;
@@ -1846,10 +1864,10 @@ template <int DIM, int B, typename T, int OP, bool STRUCT>
 void launch_one(int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
   const dim3 g((unsigned)grid), blk(64);
   // the scalar momentum form (viscous stiffness and density mass together)
-  // needs ~140 registers: capped at four waves it spilled (88 bytes per lane
+  // needs ~130 registers: capped at four waves it spilled (88 bytes per lane
   // on table bricks), uncapped it runs three without
   if constexpr (OP == K_PP || OP == K_PPS || OP == K_MASS) k_brick_o4<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
-  else if constexpr (OP == K_CH_JAC && DIM == 3 && B == 8 && STRUCT && sizeof(T) == 8)
+  else if constexpr (((OP == K_CH_JAC && STRUCT) || OP == K_VP) && DIM == 3 && B == 8 && sizeof(T) == 8)
     k_brick_o2<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
   else k_brick<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
 }
@@ -2006,6 +2024,7 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   a.sm_d = (const T*)o.sm_dinv;
   a.sm_w = (T)o.sm_w;
   a.shift = c.pp_shift;
+  if constexpr (OP == K_CH_JAC || OP == K_VP) a.fc = form_const<DIM, T>(a.phys);
   a.diag_of = o.diag_of;
   a.sy = dm.side + 1;
   a.sz = (int64_t)(dm.side + 1) * (dm.side + 1);
