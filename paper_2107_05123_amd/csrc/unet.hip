@@ -38,6 +38,7 @@ namespace chns {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kLayers = 14;
 constexpr int kInCh = 8;
@@ -172,13 +173,97 @@ __device__ __forceinline__ int conv_tile(int& ox, int& oy, int& oz, int parts) {
 }
 constexpr int kHX = kTX + 2, kHY = kTY + 2, kHZ = kTZ + 2;
 constexpr int kHRow = 40;  // bf16 per halo voxel: 32 channels + 8 padding (bank spread)
+
+// Staging of a halo of PARTS 16-byte pieces per voxel (PARTS 1, 2 or 4).  The
+// 16 inner voxels of 4 / PARTS rows are one load of a wave, so a row's address
+// is formed once per load (in scalar registers for PARTS = 4) and a lane adds
+// a fixed offset; the rows' end voxels follow, packed.  Loads and LDS stores
+// are separate calls: a thread has all its loads in flight at once, and the
+// next channel chunk's during the products of this one.
+template <int PARTS>
+struct Halo {
+  static constexpr int kRows = kHZ * kHY;
+  static constexpr int R = 4 / PARTS, NG = kRows / R, NM = (NG + 3) / 4;   // inner voxels
+  static constexpr int NEP = kRows * 2 * PARTS, NE = (NEP + 255) / 256;    // end voxels
+  u32x4 t[NM + NE];
+  // piece j of this thread
+  __device__ __forceinline__ static bool piece(int j, int wave, int lane, int& row, int& hx, int& part) {
+    if (j < NM) {
+      const int grp = wave + 4 * j;
+      row = grp * R + lane / (16 * PARTS);
+      hx = 1 + lane / PARTS % 16;
+      part = lane % PARTS;
+      return grp < NG;
+    }
+    const int i = (j - NM) * 256 + wave * 64 + lane;
+    row = i / (2 * PARTS);
+    hx = (i / PARTS & 1) * (kHX - 1);
+    part = i % PARTS;
+    return i < NEP;
+  }
+  // channels k0 + 8 part ..: below ci_up from `up`, below ci from `in`, zero beyond
+  __device__ __forceinline__ void load(int wave, int lane, int ox, int oy, int oz, int E, const uint16_t* in,
+                                       int cs_in, int ci, const uint16_t* up, int cs_up, int ci_up, int k0) {
+#pragma unroll
+    for (int j = 0; j < NM + NE; ++j) {
+      int row, hx, part;
+      const bool own = piece(j, wave, lane, row, hx, part);
+      const int x = ox + hx - 1, y = oy + row % kHY - 1, z = oz + row / kHY - 1, k = k0 + part * 8;
+      const bool low = k < ci_up;
+      const int h = E >> 1;
+      const uint16_t* q = low ? up + (int64_t)(x >> 1) * cs_up : in + (int64_t)x * cs_in;
+      const int vi = (z * E + y) * E, vu = ((z >> 1) * h + (y >> 1)) * h;
+      t[j] = u32x4{0u, 0u, 0u, 0u};
+      if (own && k < ci && (unsigned)x < (unsigned)E && (unsigned)y < (unsigned)E && (unsigned)z < (unsigned)E)
+        t[j] = *(const u32x4*)(q + (int64_t)(low ? vu : vi) * (low ? cs_up : cs_in) + k);
+    }
+  }
+  template <int ROW>
+  __device__ __forceinline__ void store(int wave, int lane, uint16_t* H) const {
+#pragma unroll
+    for (int j = 0; j < NM + NE; ++j) {
+      int row, hx, part;
+      if (piece(j, wave, lane, row, hx, part)) *(u32x4*)&H[(row * kHX + hx) * ROW + part * 8] = t[j];
+    }
+  }
+};
+
+// Stores the slice of a wave: the products have the weights as their row
+// operand, so lane (r16, g) holds channels 4 g .. 4 g + 3 of voxel x = r16 in
+// each block and writes them as eight bytes
 template <int NB>
-__global__ __launch_bounds__(256) void k_conv3_tile(const uint16_t* __restrict__ in, int cs_in, int ci,
+__device__ __forceinline__ void conv_store(const f32x4 (&acc)[4][NB], uint16_t* out, int cs_out, int x, int oy, int z,
+                                           int n, int E, int relu) {
+  if (x >= E || z >= E) return;
+#pragma unroll
+  for (int mb = 0; mb < 4; ++mb) {
+    const int y = oy + mb;
+    if (y >= E) break;
+    uint16_t* q = out + ((int64_t)(z * E + y) * E + x) * cs_out + n;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      uint32_t b[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) b[r] = f2bf(relu ? fmaxf(acc[mb][nb][r], 0.0f) : acc[mb][nb][r]);
+      *(u32x2*)(q + nb * 16) = u32x2{b[0] | b[1] << 16, b[2] | b[3] << 16};
+    }
+  }
+}
+
+// Bound for few output channels by the LDS reads (1 KiB a fragment, as long as
+// the one MFMA a SIMD gets from it), the weights' loads (as many bytes again,
+// from L1) and the staging in turn, overlapped by the other waves: three per
+// SIMD are kept for one output block (LDS admits no more), two for two.  With
+// a row's address formed once, the next chunk in flight and eight-byte stores,
+// 48 -> 16 channels at 128^3 takes 175 us (190 before), 16 -> 16 channels 63
+// (77), and a forward pass at 128^3 634 us (705)
+template <int NB>
+__global__ __launch_bounds__(256, NB == 1 ? 3 : NB == 2 ? 2 : 1) void k_conv3_tile(const uint16_t* __restrict__ in, int cs_in, int ci,
                                                     const uint16_t* __restrict__ up, int cs_up, int ci_up,
                                                     const uint16_t* __restrict__ wt, uint16_t* __restrict__ out,
                                                     int cs_out, int parts, int E, int relu) {
   __shared__ __attribute__((aligned(16))) uint16_t H[kHZ * kHY * kHX * kHRow];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, g = lane >> 4;
   const int co = NB * 16 * parts;
   int ox, oy, oz;
@@ -190,31 +275,12 @@ __global__ __launch_bounds__(256) void k_conv3_tile(const uint16_t* __restrict__
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int nchunk = (ci + 31) >> 5;
+  Halo<4> halo;
+  halo.load(wave, lane, ox, oy, oz, E, in, cs_in, ci, up, cs_up, ci_up, 0);
   for (int c = 0; c < nchunk; ++c) {
-    // stage the halo of this channel chunk: 4 rows of 16 bytes per voxel;
-    // a thread issues all its loads before its first LDS store
-    constexpr int NS = kHZ * kHY * kHX * 4, NJ = (NS + 255) / 256;
-    u32x4 t[NJ];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int i = tid + j * 256;
-      const int hv = i >> 2, part = i & 3;
-      const int hx = hv % kHX, hy = (hv / kHX) % kHY, hz = hv / (kHX * kHY);
-      const int x = ox + hx - 1, y = oy + hy - 1, z = oz + hz - 1;
-      const int k = c * 32 + part * 8;
-      t[j] = u32x4{0u, 0u, 0u, 0u};
-      if (i < NS && k < ci && x >= 0 && x < E && y >= 0 && y < E && z >= 0 && z < E) {
-        const int h = E / 2;
-        t[j] = *(const u32x4*)(k < ci_up ? up + ((int64_t)((z / 2) * h + y / 2) * h + x / 2) * cs_up + k
-                                         : in + ((int64_t)(z * E + y) * E + x) * cs_in + k);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int i = tid + j * 256;
-      if (i < NS) *(u32x4*)&H[(i >> 2) * kHRow + (i & 3) * 8] = t[j];
-    }
+    halo.store<kHRow>(wave, lane, H);
     __syncthreads();
+    if (c + 1 < nchunk) halo.load(wave, lane, ox, oy, oz, E, in, cs_in, ci, up, cs_up, ci_up, (c + 1) * 32);
     const int k0 = c * 32 + g * 8;
     const bool kin = k0 < ci;
     if constexpr (NB <= 2) {
@@ -248,7 +314,7 @@ __global__ __launch_bounds__(256) void k_conv3_tile(const uint16_t* __restrict__
               if (mb < 0 || mb >= kTY) continue;
 #pragma unroll
               for (int nb = 0; nb < NB; ++nb)
-                acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf(w[(dy + 1) * 3 + dx + 1][nb]),
+                acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(w[(dy + 1) * 3 + dx + 1][nb]), av,
                                                                      acc[mb][nb], 0, 0, 0);
             }
           }
@@ -281,30 +347,13 @@ __global__ __launch_bounds__(256) void k_conv3_tile(const uint16_t* __restrict__
           const bf16x8 av = as_bf(ta);
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb)
-            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf(w[t][nb]), acc[mb][nb], 0, 0, 0);
+            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(w[t][nb]), av, acc[mb][nb], 0, 0, 0);
         }
       }
     }
     __syncthreads();
   }
-  // lane holds rows 4 g + r (x offsets) of column r16 (channel) of each block
-  const int z = oz + wave;
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    const int y = oy + mb;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int x = ox + 4 * g + r;
-      if (x >= E || y >= E || z >= E) continue;
-      const int64_t v = (int64_t)(z * E + y) * E + x;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        float val = acc[mb][nb][r];
-        if (relu) val = fmaxf(val, 0.0f);
-        out[v * cs_out + n0 + nb * 16 + r16] = f2bf(val);
-      }
-    }
-  }
+  conv_store<NB>(acc, out, cs_out, ox + r16, oy, oz + wave, n0 + 4 * g, E, relu);
 }
 
 // Small input-channel counts (ci = 8, 16, 32; 48 with 48 output channels,
@@ -322,21 +371,23 @@ __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__
   constexpr int NQ = (KT + 31) / 32;
   constexpr int QG = NB <= 1 ? NQ : (NB <= 2 ? 9 : 3);  // chunks whose weights load together
   __shared__ __attribute__((aligned(16))) uint16_t H[kHZ * kHY * kHX * ROW];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, g = lane >> 4;
   const int co = NB * 16 * parts;
   int ox, oy, oz;
   const int n0 = conv_tile(ox, oy, oz, parts) * NB * 16;
   wt += (int64_t)n0 * CI;
-  if constexpr (CI >= 32) {
-    // all loads of a thread before its first LDS store (measured faster
-    // for 32 and 48 channels; for 16 the unrolled loads cost occupancy); the
-    // fence keeps the weight loads below out of this phase
+  if constexpr (CI <= 32) {
+    Halo<PARTS> halo;
+    halo.load(wave, lane, ox, oy, oz, E, in, cs_in, CI, nullptr, 0, 0, 0);
+    halo.template store<ROW>(wave, lane, H);
+  } else {
+    // six pieces to a voxel
     constexpr int NS = kHZ * kHY * kHX * PARTS, NJ = (NS + 255) / 256;
     u32x4 t[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const int i = tid + j * 256;
+      const int i = threadIdx.x + j * 256;
       const int hv = i / PARTS, part = i % PARTS;
       const int hx = hv % kHX, hy = (hv / kHX) % kHY, hz = hv / (kHX * kHY);
       const int x = ox + hx - 1, y = oy + hy - 1, z = oz + hz - 1;
@@ -346,21 +397,12 @@ __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__
     }
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const int i = tid + j * 256;
+      const int i = threadIdx.x + j * 256;
       if (i < NS) *(u32x4*)&H[(i / PARTS) * ROW + (i % PARTS) * 8] = t[j];
     }
-    asm volatile("" ::: "memory");
-  } else {
-    for (int i = tid; i < kHZ * kHY * kHX * PARTS; i += 256) {
-      const int hv = i / PARTS, part = i % PARTS;
-      const int hx = hv % kHX, hy = (hv / kHX) % kHY, hz = hv / (kHX * kHY);
-      const int x = ox + hx - 1, y = oy + hy - 1, z = oz + hz - 1;
-      u32x4 t = {0u, 0u, 0u, 0u};
-      if (x >= 0 && x < E && y >= 0 && y < E && z >= 0 && z < E)
-        t = *(const u32x4*)(in + ((int64_t)(z * E + y) * E + x) * cs_in + part * 8);
-      *(u32x4*)&H[hv * ROW + part * 8] = t;
-    }
   }
+  // keeps the weight loads below out of the staging
+  asm volatile("" ::: "memory");
   __syncthreads();
   f32x4 acc[4][NB];
 #pragma unroll
@@ -395,27 +437,11 @@ __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__
         const bf16x8 av = as_bf(ta);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf(w[qq][nb]), acc[mb][nb], 0, 0, 0);
+          acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(w[qq][nb]), av, acc[mb][nb], 0, 0, 0);
       }
     }
   }
-  const int z = oz + wave;
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    const int y = oy + mb;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int x = ox + 4 * g + r;
-      if (x >= E || y >= E || z >= E) continue;
-      const int64_t v = (int64_t)(z * E + y) * E + x;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        float val = acc[mb][nb][r];
-        if (relu) val = fmaxf(val, 0.0f);
-        out[v * cs_out + n0 + nb * 16 + r16] = f2bf(val);
-      }
-    }
-  }
+  conv_store<NB>(acc, out, cs_out, ox + r16, oy, oz + wave, n0 + 4 * g, E, relu);
 }
 
 // Weight gradient: partial[s][tap][i][j] = sum over this split's voxels v of
