@@ -356,6 +356,54 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : NB == 2 ? 2 : 1) void k_conv3_ti
   conv_store<NB>(acc, out, cs_out, ox + r16, oy, oz + wave, n0 + 4 * g, E, relu);
 }
 
+// Mean of the 2 x 2 x 2 children of the slices a workgroup has just formed,
+// from registers: lane pairs hold the x neighbours, one wave both y and the
+// next wave the other z, which adds its four values to the sums of the even
+// wave read from LDS (`sm`, the halo, no longer needed).  As a pass of its own
+// over the stored voxels the three poolings of a forward pass at 128^3 took
+// 51 us.  The order of the eight sums is that of (z, y, x).
+template <int NB>
+__device__ __forceinline__ void conv_pool(const f32x4 (&acc)[4][NB], uint16_t* pool, int cs, uint16_t* sm, int wave,
+                                          int lane, int x, int oy, int z, int n, int E, int relu) {
+  const bool even = !(wave & 1);
+  f32x4* buf = (f32x4*)sm + wave / 2 * (2 * NB * 64) + lane;
+  __syncthreads();
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    if (even == (pass == 0)) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          f32x4 s = {0.f, 0.f, 0.f, 0.f};
+          if (pass == 1) s = buf[(p * NB + nb) * 64];
+#pragma unroll
+          for (int yy = 0; yy < 2; ++yy)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float a = acc[2 * p + yy][nb][r];
+              const float v = bf2f(f2bf(relu ? fmaxf(a, 0.0f) : a));
+              s[r] += v;
+              s[r] += __shfl_xor(v, 1, 64);
+            }
+          if (pass == 0) {
+            buf[(p * NB + nb) * 64] = s;
+          } else {
+            const int y = oy + 2 * p;
+            if ((lane & 1) || x >= E || y >= E || z >= E) continue;
+            uint32_t b[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) b[r] = f2bf(s[r] * 0.125f);
+            const int h = E / 2;
+            *(u32x2*)(pool + ((int64_t)((z / 2) * h + y / 2) * h + x / 2) * cs + n + nb * 16) =
+                u32x2{b[0] | b[1] << 16, b[2] | b[3] << 16};
+          }
+        }
+    }
+    if (pass == 0) __syncthreads();
+  }
+}
+
 // Small input-channel counts (ci = 8, 16, 32; 48 with 48 output channels,
 // where the 73 KB halo still leaves enough occupancy): the whole halo (all
 // channels) fits in LDS, and K = 27 taps x ci is one flat dimension, k = tap ci + c, cut
@@ -364,7 +412,8 @@ __global__ __launch_bounds__(256, NB == 1 ? 3 : NB == 2 ? 2 : 1) void k_conv3_ti
 template <int NB, int CI>
 __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__ in, int cs_in,
                                                     const uint16_t* __restrict__ wt, uint16_t* __restrict__ out,
-                                                    int cs_out, int parts, int E, int relu) {
+                                                    int cs_out, uint16_t* __restrict__ pool, int parts, int E,
+                                                    int relu) {
   constexpr int ROW = CI + 8;  // bf16 per halo voxel (8 padding: bank spread, 16-byte rows)
   constexpr int PARTS = CI / 8;
   constexpr int KT = 27 * CI;
@@ -442,6 +491,8 @@ __global__ __launch_bounds__(256) void k_conv3_flat(const uint16_t* __restrict__
     }
   }
   conv_store<NB>(acc, out, cs_out, ox + r16, oy, oz + wave, n0 + 4 * g, E, relu);
+  if constexpr (NB * 16 <= CI)
+    if (pool) conv_pool<NB>(acc, pool, co, H, wave, lane, ox + r16, oy, oz + wave, n0 + 4 * g, E, relu);
 }
 
 // Weight gradient: partial[s][tap][i][j] = sum over this split's voxels v of
@@ -603,28 +654,6 @@ __device__ __forceinline__ u32x4 pack8(const float* f) {
   return t;
 }
 
-// P[z][y][x][c] = mean of the 2x2x2 children (coarse edge Ec)
-__global__ void k_pool(const uint16_t* in, int cs_in, uint16_t* out, int C, int Ec) {
-  const int G = C / 8;
-  const int64_t n = (int64_t)Ec * Ec * Ec * G;
-  const int Ef = 2 * Ec;
-  ULOOP(idx, n) {
-    const int grp = (int)(idx % G);
-    const int p = (int)(idx / G);
-    const int x = p % Ec, y = (p / Ec) % Ec, z = p / (Ec * Ec);
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < 8; ++k) {
-      const int fz = 2 * z + (k >> 2), fy = 2 * y + ((k >> 1) & 1), fx = 2 * x + (k & 1);
-      float f[8];
-      unpack8(*(const u32x4*)(in + ((int64_t)(fz * Ef + fy) * Ef + fx) * cs_in + grp * 8), f);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) s[j] += f[j];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s[j] *= 0.125f;
-    *(u32x4*)(out + (int64_t)p * C + grp * 8) = pack8(s);
-  }
-}
 // dskip[v][c] += dP[parent(v)][c] / 8 (fine edge Ef)
 __global__ void k_pool_bwd_add(const uint16_t* dP, int C, uint16_t* dskip, int cs, int Ef) {
   const int G = C / 8;
@@ -1054,23 +1083,31 @@ __global__ void k_gbeta(double* gn, const double* G, const double* r1, const dou
 
 // ------------------------------------------------------------ host side
 // up (or null): channels below ci_up read from the half-resolution grid.
+// pool (or null): also the means of 2 x 2 x 2 voxels, co channels on the
+// half-resolution grid (E even); k_conv3_flat forms them, where co <= ci.
 // A workgroup forms all output channels of its tile while there are tiles
 // enough for the chip (a fragment then feeds every column block); on the small
 // grids each 16-channel block gets a workgroup of its own (E = 16, 64 -> 64
 // channels: 16 workgroups, 30 us; 64, 14 us).  The order of the sums is the
 // same either way.
 int conv(const uint16_t* in, int cs_in, int ci, const uint16_t* wt, uint16_t* out, int cs_out, int co, int E,
-         bool relu, hipStream_t s, const uint16_t* up = nullptr, int cs_up = 0, int ci_up = 0) {
+         bool relu, hipStream_t s, const uint16_t* up = nullptr, int cs_up = 0, int ci_up = 0,
+         uint16_t* pool = nullptr) {
   const int r = relu ? 1 : 0;
   const unsigned tx = (unsigned)((E + kTX - 1) / kTX), ty = (unsigned)((E + kTY - 1) / kTY),
                  tz = (unsigned)((E + kTZ - 1) / kTZ);
   const int nb = co / 16, parts = tx * ty * tz < 256 ? nb : 1;
   const dim3 g(tx, ty, tz * parts);
   const int key = nb / parts * 100 + ci;
-  if (!up && (ci == 8 || ci == 16 || ci == 32 || (ci == 48 && nb == 3))) {
+  const bool flat = !up && (ci == 8 || ci == 16 || ci == 32 || (ci == 48 && nb == 3));
+  if (pool && (!flat || co > ci || E % 2 != 0)) {
+    set_error("unsupported channel count");
+    return CHNS_EINVAL;
+  }
+  if (flat) {
     switch (key) {
 #define FL(b, cc) \
-  case b * 100 + cc: k_conv3_flat<b, cc><<<g, 256, 0, s>>>(in, cs_in, wt, out, cs_out, parts, E, r); break;
+  case b * 100 + cc: k_conv3_flat<b, cc><<<g, 256, 0, s>>>(in, cs_in, wt, out, cs_out, pool, parts, E, r); break;
       FL(1, 8) FL(1, 16) FL(1, 32) FL(1, 48) FL(2, 16) FL(2, 32) FL(3, 32) FL(5, 32) FL(3, 16) FL(3, 48)
 #undef FL
       default:
@@ -1200,6 +1237,9 @@ int forward(UNet& u, UActs& a, hipStream_t s) {
   int rc;
 #define CV(in, csi, k, out, cso, E) \
   if ((rc = conv(in, csi, L[k].ci, L[k].wf, out, cso, L[k].co, E, true, s))) return rc;
+  // the last convolution of a level also pools
+#define CP(in, csi, k, out, cso, E, pool)                                                                           \
+  if ((rc = conv(in, csi, L[k].ci, L[k].wf, out, cso, L[k].co, E, true, s, nullptr, 0, 0, pool))) return rc;
   // the first convolution after a concatenation reads its upsampled channels
   // from the coarse grid; with gradients to come the weight gradient needs
   // them in place
@@ -1207,14 +1247,11 @@ int forward(UNet& u, UActs& a, hipStream_t s) {
   if (a.grads) k_up<<<nblk((int64_t)(E) * (E) * (E) * (cu) / 8), kT, 0, s>>>(low, cu, cat, csi, E);               \
   if ((rc = conv(cat, csi, L[k].ci, L[k].wf, out, cso, L[k].co, E, true, s, low, cu, cu))) return rc;
   CV(a.X, kInCh, 0, a.A0, 16, E0);
-  CV(a.A0, 16, 1, a.cat0 + 32, 48, E0);
-  k_pool<<<nblk((int64_t)E1 * E1 * E1 * 2), kT, 0, s>>>(a.cat0 + 32, 48, a.P0, 16, E1);
+  CP(a.A0, 16, 1, a.cat0 + 32, 48, E0, a.P0);
   CV(a.P0, 16, 2, a.A2, 32, E1);
-  CV(a.A2, 32, 3, a.cat1 + 48, 80, E1);
-  k_pool<<<nblk((int64_t)E2 * E2 * E2 * 4), kT, 0, s>>>(a.cat1 + 48, 80, a.P1, 32, E2);
+  CP(a.A2, 32, 3, a.cat1 + 48, 80, E1, a.P1);
   CV(a.P1, 32, 4, a.A4, 48, E2);
-  CV(a.A4, 48, 5, a.cat2 + 64, 112, E2);
-  k_pool<<<nblk((int64_t)E3 * E3 * E3 * 6), kT, 0, s>>>(a.cat2 + 64, 112, a.P2, 48, E3);
+  CP(a.A4, 48, 5, a.cat2 + 64, 112, E2, a.P2);
   CV(a.P2, 48, 6, a.A6, 64, E3);
   CV(a.A6, 64, 7, a.A7, 64, E3);
   CU(a.A7, 64, a.cat2, 112, 8, a.A8, 48, E2);
@@ -1224,6 +1261,7 @@ int forward(UNet& u, UActs& a, hipStream_t s) {
   CU(a.A11, 32, a.cat0, 48, 12, a.A12, 16, E0);
   CV(a.A12, 16, 13, a.A13, 16, E0);
 #undef CV
+#undef CP
 #undef CU
   CHNS_HIP(hipGetLastError());
   return CHNS_OK;
