@@ -96,6 +96,16 @@ template <typename T>
 __global__ void k_dense(const T* M, const T* r, T* z, int n) {
   for (int i = blockIdx.x * kT + threadIdx.x; i < n; i += gridDim.x * kT) z[i] = dense_row<T>(M, r, i, n);
 }
+// Coordinates of a node of a uniform level of side s.  Node numbers are below
+// 2^31, so the divisions are 32-bit: in 64 bits they were most of the
+// transfer kernels' instructions.
+template <int DIM>
+__device__ __forceinline__ void node_ijk(int64_t node, int s, int& I, int& J, int& K) {
+  const uint32_t s1 = s + 1, v = (uint32_t)node, q = v / s1;
+  I = (int)(v - q * s1);
+  J = (int)(DIM == 3 ? q % s1 : q);
+  K = (int)(DIM == 3 ? q / s1 : 0);
+}
 // Structured transfers between uniform lexicographically numbered levels
 // (fine side nf = 2 nc nodes per edge minus one): the Q1 embedding has weight
 // 1 at coincident nodes and 1/2 per direction at midpoints.
@@ -106,37 +116,45 @@ __global__ void k_dense(const T* M, const T* r, T* z, int n) {
 // that every load is unconditional and a thread issues all of them at once
 // (on the small levels nothing else hides their latency); the added zeros
 // leave the sums unchanged.
+// With the test for t outside the loads and 32-bit indices the four
+// restrictions of a level-7 cycle take 25 us (38 with 64-bit divisions and a
+// branch per neighbour), the whole solve at 128^3 3.30 ms (3.56).
 template <typename T, int DIM>
 __device__ __forceinline__ T restrict_at(const T* __restrict__ r, const T* __restrict__ t, int64_t c, int nc) {
-  const int nf = 2 * nc;
-  const int64_t s1 = nc + 1, f1 = nf + 1;
-  {
-    const int I = (int)(c % s1), J = (int)((c / s1) % s1), K = DIM == 3 ? (int)(c / (s1 * s1)) : 0;
-    T acc = T(0);
+  constexpr int NS = DIM == 3 ? 27 : 9;
+  const int nf = 2 * nc, f1 = nf + 1;
+  int I, J, K;
+  node_ijk<DIM>(c, nc, I, J, K);
+  // weights and clamped indices of the three neighbours along each axis (the
+  // weights are powers of two: their products are exact)
+  T wx[3], wy[3], wz[3];
+  int ix[3], iy[3], iz[3];
 #pragma unroll
-    for (int cz = (DIM == 3 ? -1 : 0); cz <= (DIM == 3 ? 1 : 0); ++cz) {
-      const int k = 2 * K + cz;
-      const T wz = (k < 0 || k > nf) ? T(0) : (cz ? T(0.5) : T(1));
-      const int kk = min(max(k, 0), nf);
-#pragma unroll
-      for (int cy = -1; cy <= 1; ++cy) {
-        const int j = 2 * J + cy;
-        const T wy = (j < 0 || j > nf) ? T(0) : (cy ? wz * T(0.5) : wz);
-        const int64_t row = ((int64_t)kk * f1 + min(max(j, 0), nf)) * f1;
-#pragma unroll
-        for (int cx = -1; cx <= 1; ++cx) {
-          const int i = 2 * I + cx;
-          const T w = (i < 0 || i > nf) ? T(0) : (cx ? wy * T(0.5) : wy);
-          const int64_t ii = row + min(max(i, 0), nf);
-          acc += w * (t ? r[ii] - t[ii] : r[ii]);
-        }
-      }
-    }
-    return acc;
+  for (int o = 0; o < 3; ++o) {
+    const int i = 2 * I + o - 1, j = 2 * J + o - 1, k = 2 * K + o - 1;
+    const T h = o == 1 ? T(1) : T(0.5);
+    wx[o] = i < 0 || i > nf ? T(0) : h;
+    wy[o] = j < 0 || j > nf ? T(0) : h;
+    wz[o] = k < 0 || k > nf ? T(0) : h;
+    ix[o] = min(max(i, 0), nf);
+    iy[o] = min(max(j, 0), nf) * f1;
+    iz[o] = min(max(k, 0), nf) * f1 * f1;
   }
+  const auto at = [&](int o) { return ix[o % 3] + iy[o / 3 % 3] + (DIM == 3 ? iz[o / 9] : 0); };
+  T v[NS];
+#pragma unroll
+  for (int o = 0; o < NS; ++o) v[o] = r[at(o)];
+  if (t) {
+#pragma unroll
+    for (int o = 0; o < NS; ++o) v[o] -= t[at(o)];
+  }
+  T acc = T(0);
+#pragma unroll
+  for (int o = 0; o < NS; ++o) acc += wx[o % 3] * wy[o / 3 % 3] * (DIM == 3 ? wz[o / 9] : T(1)) * v[o];
+  return acc;
 }
 template <typename T, int DIM>
-__global__ void k_restrict_s(const T* __restrict__ r, const T* __restrict__ t, T* __restrict__ out, int nc) {
+__global__ __launch_bounds__(kT) void k_restrict_s(const T* __restrict__ r, const T* __restrict__ t, T* __restrict__ out, int nc) {
   const int64_t s1 = nc + 1;
   const int64_t ncount = DIM == 3 ? s1 * s1 * s1 : s1 * s1;
   for (int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x; c < ncount; c += (int64_t)gridDim.x * kT)
@@ -145,10 +163,12 @@ __global__ void k_restrict_s(const T* __restrict__ r, const T* __restrict__ t, T
 // coarse-field value at fine node f (bilinear / trilinear interpolation)
 template <typename T>
 __device__ __forceinline__ T prolong_at(const T* __restrict__ zc, int64_t f, int nc, int dim) {
-  const int64_t s1 = nc + 1, f1 = 2 * nc + 1;
-  const int i = (int)(f % f1), j = (int)((f / f1) % f1), k = dim == 3 ? (int)(f / (f1 * f1)) : 0;
+  const int s1 = nc + 1;
+  int i, j, k;
+  if (dim == 3) node_ijk<3>(f, 2 * nc, i, j, k);
+  else node_ijk<2>(f, 2 * nc, i, j, k);
   const int i0 = i >> 1, i1 = (i + 1) >> 1, j0 = j >> 1, j1 = (j + 1) >> 1, k0 = k >> 1, k1 = (k + 1) >> 1;
-  auto at = [&](int a, int b, int c) { return zc[((int64_t)c * s1 + b) * s1 + a]; };
+  auto at = [&](int a, int b, int c) { return zc[(c * s1 + b) * s1 + a]; };
   if (dim == 3)
     return T(0.125) * ((at(i0, j0, k0) + at(i1, j0, k0)) + (at(i0, j1, k0) + at(i1, j1, k0)) +
                        (at(i0, j0, k1) + at(i1, j0, k1)) + (at(i0, j1, k1) + at(i1, j1, k1)));
@@ -165,8 +185,10 @@ __global__ void k_inject_s(const double* __restrict__ fine, double* __restrict__
   const int64_t s1 = nc + 1, f1 = 2 * nc + 1;
   const int64_t ncount = dim == 3 ? s1 * s1 * s1 : s1 * s1;
   for (int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x; c < ncount; c += (int64_t)gridDim.x * kT) {
-    const int64_t I = c % s1, J = (c / s1) % s1, K = dim == 3 ? c / (s1 * s1) : 0;
-    out[c] = fine[((2 * K) * f1 + 2 * J) * f1 + 2 * I];
+    int I, J, K;
+    if (dim == 3) node_ijk<3>(c, nc, I, J, K);
+    else node_ijk<2>(c, nc, I, J, K);
+    out[c] = fine[((int64_t)(2 * K) * f1 + 2 * J) * f1 + 2 * I];
   }
 }
 
@@ -429,7 +451,8 @@ __global__ void k_diag_gather(const double* __restrict__ DP, int sc, double* din
   const int64_t f1 = sf + 1;
   const int64_t n = DIM == 3 ? f1 * f1 * f1 : f1 * f1;
   for (int64_t node = (int64_t)blockIdx.x * kT + threadIdx.x; node < n; node += (int64_t)gridDim.x * kT) {
-    const int P[3] = {(int)(node % f1), (int)((node / f1) % f1), DIM == 3 ? (int)(node / (f1 * f1)) : 0};
+    int P[3];
+    node_ijk<DIM>(node, sf, P[0], P[1], P[2]);
     // per axis: (coarse index, local index) options
     int ce[3][2], lo[3][2], no[3];
     for (int d = 0; d < 3; ++d) {
@@ -517,7 +540,8 @@ __global__ void k_el_stencil(const double* __restrict__ E, int s, double* S64, f
   const int64_t s1 = s + 1;
   const int64_t n = DIM == 3 ? s1 * s1 * s1 : s1 * s1;
   for (int64_t node = (int64_t)blockIdx.x * kT + threadIdx.x; node < n; node += (int64_t)gridDim.x * kT) {
-    const int I = (int)(node % s1), J = (int)((node / s1) % s1), K = DIM == 3 ? (int)(node / (s1 * s1)) : 0;
+    int I, J, K;
+    node_ijk<DIM>(node, s, I, J, K);
     double acc[NS];
 #pragma unroll
     for (int o = 0; o < NS; ++o) acc[o] = 0.0;
@@ -570,55 +594,55 @@ __global__ void k_stencil_dense(const double* __restrict__ S, int s, double* M) 
 // Index of the neighbour at offset (ox, oy, oz), clamped into the level: the
 // stencil value of an offset outside the level is 0, so every load can be
 // unconditional (all issued at once) and the sum is the same.
+// keeps the loads before it in flight together: left alone, the compiler sinks
+// each to its use
+__device__ __forceinline__ void load_fence() { asm volatile("" ::: "memory"); }
 template <int DIM>
-__device__ __forceinline__ int64_t nbr(int64_t node, int ox, int oy, int oz, int64_t s1, int64_t n) {
-  const int64_t j = node + ox + oy * s1 + (DIM == 3 ? oz * s1 * s1 : 0);
-  return j < 0 ? 0 : (j >= n ? n - 1 : j);
+__device__ __forceinline__ int nbr(int node, int ox, int oy, int oz, int s1, int n) {
+  return min(max(node + ox + oy * s1 + (DIM == 3 ? oz * s1 * s1 : 0), 0), n - 1);
 }
 template <typename T, int DIM, typename ST>
 __device__ __forceinline__ T stencil_row(const ST* __restrict__ S, const T* __restrict__ v, int64_t node, int64_t n,
                                          int I, int J, int K, int s) {
-  const int64_t s1 = s + 1;
+  const int s1 = s + 1, i = (int)node, last = (int)n;
+  constexpr int NS = DIM == 3 ? 27 : 9;
+  ST a[NS];
+  T x[NS];
+#pragma unroll
+  for (int o = 0; o < NS; ++o) {
+    a[o] = (S + o * n)[i];
+    x[o] = v[nbr<DIM>(i, o % 3 - 1, o / 3 % 3 - 1, DIM == 3 ? o / 9 - 1 : 0, s1, last)];
+  }
+  load_fence();
   T acc = T(0);
 #pragma unroll
-  for (int oz = (DIM == 3 ? -1 : 0); oz <= (DIM == 3 ? 1 : 0); ++oz) {
-#pragma unroll
-    for (int oy = -1; oy <= 1; ++oy) {
-#pragma unroll
-      for (int ox = -1; ox <= 1; ++ox) {
-        const int o = (ox + 1) + 3 * (oy + 1) + (DIM == 3 ? 9 * (oz + 1) : 0);
-        acc += (T)S[o * n + node] * v[nbr<DIM>(node, ox, oy, oz, s1, n)];
-      }
-    }
-  }
+  for (int o = 0; o < NS; ++o) acc += (T)a[o] * x[o];
   return acc;
-}
-template <int DIM>
-__device__ __forceinline__ void node_ijk(int64_t node, int s, int& I, int& J, int& K) {
-  const int64_t s1 = s + 1;
-  I = (int)(node % s1);
-  J = (int)((node / s1) % s1);
-  K = DIM == 3 ? (int)(node / (s1 * s1)) : 0;
 }
 // Per-node bodies of the stencil smoothers, shared by the per-level kernels
 // below and the fused coarse tail (the same arithmetic in both).
 // (A w D^-1 r)(i): the image of the first damped-Jacobi sweep from z = 0
-template <typename T, int DIM, typename ST>
+template <typename T, int DIM, typename ST, int PL = 3>
 __device__ __forceinline__ T first_sweep_image(const ST* __restrict__ S, const T* __restrict__ dinv,
                                                const T* __restrict__ r, T w, int64_t i, int s, int64_t n) {
-  const int64_t s1 = s + 1;
+  const int s1 = s + 1, c = (int)i, last = (int)n;
+  constexpr int NS = DIM == 3 ? 27 : 9, NP = DIM == 3 ? PL : 1;  // neighbours, load phases
   T az = T(0);
 #pragma unroll
-  for (int oz = (DIM == 3 ? -1 : 0); oz <= (DIM == 3 ? 1 : 0); ++oz) {
+  for (int p = 0; p < NP; ++p) {
+    ST a[NS / NP];
+    T d[NS / NP], x[NS / NP];
 #pragma unroll
-    for (int oy = -1; oy <= 1; ++oy) {
-#pragma unroll
-      for (int ox = -1; ox <= 1; ++ox) {
-        const int o = (ox + 1) + 3 * (oy + 1) + (DIM == 3 ? 9 * (oz + 1) : 0);
-        const int64_t j = nbr<DIM>(i, ox, oy, oz, s1, n);
-        az += (T)S[o * n + i] * (w * dinv[j] * r[j]);
-      }
+    for (int k = 0; k < NS / NP; ++k) {
+      const int o = p * (NS / NP) + k;
+      const int j = nbr<DIM>(c, o % 3 - 1, o / 3 % 3 - 1, DIM == 3 ? o / 9 - 1 : 0, s1, last);
+      a[k] = (S + o * n)[c];
+      d[k] = dinv[j];
+      x[k] = r[j];
     }
+    load_fence();
+#pragma unroll
+    for (int k = 0; k < NS / NP; ++k) az += (T)a[k] * (w * d[k] * x[k]);
   }
   return az;
 }
@@ -653,16 +677,16 @@ __global__ void k_st_pre2(const ST* __restrict__ S, const T* __restrict__ dinv, 
 }
 // one damped-Jacobi sweep from z = 0 and its image: z = w D^-1 r, t = A z
 template <typename T, int DIM, typename ST>
-__global__ void k_st_pre1(const ST* __restrict__ S, const T* __restrict__ dinv, const T* __restrict__ r,
+__global__ __launch_bounds__(kT) void k_st_pre1(const ST* __restrict__ S, const T* __restrict__ dinv, const T* __restrict__ r,
                           T* __restrict__ z, T* __restrict__ t, T w, int s, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT) {
     z[i] = w * dinv[i] * r[i];
-    t[i] = first_sweep_image<T, DIM, ST>(S, dinv, r, w, i, s, n);
+    t[i] = first_sweep_image<T, DIM, ST, 1>(S, dinv, r, w, i, s, n);
   }
 }
 // zo = zi + w D^-1 (r - A zi)
 template <typename T, int DIM, typename ST>
-__global__ void k_st_sweep(const ST* __restrict__ S, const T* __restrict__ dinv, const T* __restrict__ r,
+__global__ __launch_bounds__(kT) void k_st_sweep(const ST* __restrict__ S, const T* __restrict__ dinv, const T* __restrict__ r,
                            const T* __restrict__ zi, T* __restrict__ zo, T w, int s, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT)
     zo[i] = sweep_at<T, DIM, ST>(S, dinv, r, zi, w, i, s, n);
