@@ -48,7 +48,7 @@ PP_BYTES_PER_DOF = {8: 24, 4: 12}   # x and phi~ read once, y written once
 
 def src_hash() -> str:
     h = hashlib.sha256()
-    for f in ("apply.hip",):
+    for f in ("apply.hip", "march.h", "pp_tile.h"):
         with open(os.path.join(ROOT, "paper_2107_05123_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -212,12 +212,18 @@ def load_traffic(tag):
     return d.get("bytes_per_launch")
 
 
+def pp_kernels(es):
+    """Kernels of one pressure apply on a uniform 3D mesh: one for FP64, bricks
+    and the completion of shared nodes for FP32."""
+    return "k_pp_tile<double,PP>" if es == 8 else "k_brick_o4<3,8,float,PP> + k_combine<float,1,0>"
+
+
 def apply_roofline(n_elems, n_dof, brick_ms, combine_ms, es=8):
-    """Roofline entry of one whole pressure apply (brick kernel + combine,
-    their average durations from the library's HIP events): algorithmic
-    bytes (x, phi~ read, y written once: 24 B/DoF in FP64, 12 in FP32) and
+    """Roofline entry of one whole pressure apply (its element kernel and, if
+    it has one, its combine; average durations from the library's HIP events):
+    algorithmic bytes (x, phi~ read, y written once: 24 B/DoF in FP64, 12 in FP32) and
     flops per launch over the apply's time, against HBM and the vector ALU.
-    The brick kernel alone is kept as an extra entry."""
+    The element kernel alone is kept as an extra entry."""
     flops = PP_FLOPS_PER_LEAF * n_elems
     nbytes = PP_BYTES_PER_DOF[es] * n_dof
     ms = brick_ms + combine_ms
@@ -235,8 +241,7 @@ def apply_roofline(n_elems, n_dof, brick_ms, combine_ms, es=8):
     else:
         roof = {"bound": "hbm", "achieved": ach_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": frac_hbm,
                 "traffic": traffic}
-    prec = "double" if es == 8 else "float"
-    roof.update({"kernel": f"k_brick_o4<3,8,{prec},PP> + k_combine<{prec},1,0> (one apply)", "kernel_ms": ms,
+    roof.update({"kernel": f"{pp_kernels(es)} (one apply)", "kernel_ms": ms,
                  "algorithmic_bytes_per_launch": nbytes, "algorithmic_flops_per_launch": flops,
                  "hbm_frac_algorithmic": frac_hbm, "alu_frac": frac_alu, "gdof_s": n_dof / (ms * 1e-3) / 1e9,
                  "brick_only": {"kernel_ms": brick_ms, "alu_frac": flops / (brick_ms * 1e-3) / 1e12 / peak_alu,
@@ -267,24 +272,28 @@ def summarize_stats(db, out_md, title, command, note, limit=30):
 
 
 def summarize_pmc(fetch_csv, write_csv, out_prefix, commands):
-    """HBM bytes per pressure apply (brick kernel + combine), FP64 and FP32,
+    """HBM bytes per pressure apply (element kernel + combine), FP64 and FP32,
     from FETCH_SIZE / WRITE_SIZE passes, calibrated on the 256 MiB device copy
     of the same run (the copy reads and writes 262144 KiB)."""
     import csv
 
-    def per_kernel(path, key):
+    def per_kernel(path, *keys):
         with open(path) as fh:
-            return [float(r["Counter_Value"]) for r in csv.DictReader(fh) if key in r["Kernel_Name"]]
+            return [float(r["Counter_Value"]) for r in csv.DictReader(fh) if any(k in r["Kernel_Name"] for k in keys)]
     avg = lambda v: sum(v) / len(v) if v else 0.0
     ff = 262144.0 / max(per_kernel(fetch_csv, "copyBuffer"))
     fw = 262144.0 / max(per_kernel(write_csv, "copyBuffer"))
     out = {}
     for prec, es in (("double", 8), ("float", 4)):
-        kb, kc = f"k_brick_o4<3, 8, {prec}, 0", f"k_combine<{prec}, 1, 0>"
-        fb, wb = avg(per_kernel(fetch_csv, kb)) * ff * 1024, avg(per_kernel(write_csv, kb)) * fw * 1024
-        fc, wc = avg(per_kernel(fetch_csv, kc)) * ff * 1024, avg(per_kernel(write_csv, kc)) * fw * 1024
-        d = {"kernel": f"k_brick_o4<3,8,{prec},PP> + k_combine<{prec},1,0> (pressure-Poisson apply, 128^3)",
-             "src_hash": src_hash(), "dispatches": len(per_kernel(fetch_csv, kb)),
+        # where one kernel is the whole apply, the combine belongs to other forms
+        kb, kc = (f"k_pp_tile<{prec}",), ()
+        if not per_kernel(fetch_csv, *kb):
+            kb = (f"k_brick_o4<3, 8, {prec}, 0",)
+            kc = (f"k_combine<{prec}, 1, 0>", f"k_combine<{prec}, 1, 0, false>")
+        fb, wb = avg(per_kernel(fetch_csv, *kb)) * ff * 1024, avg(per_kernel(write_csv, *kb)) * fw * 1024
+        fc, wc = avg(per_kernel(fetch_csv, *kc)) * ff * 1024, avg(per_kernel(write_csv, *kc)) * fw * 1024
+        d = {"kernel": f"{pp_kernels(es)} (pressure-Poisson apply, 128^3)",
+             "src_hash": src_hash(), "dispatches": len(per_kernel(fetch_csv, *kb)),
              "fetch_factor": ff, "write_factor": fw,
              "calibration": "256 MiB device copy: FETCH_SIZE x fetch_factor and WRITE_SIZE x write_factor give "
                             "262144 KiB each",
