@@ -3,8 +3,9 @@
 // All scalars (dot products, step lengths, iteration count, convergence flag)
 // live in device memory; the host only enqueues kernels and polls the flag
 // every few iterations.  Dot products are accumulated in FP64 with a
-// wavefront + block tree and a last-block finalisation over the per-block
-// partials in a fixed order, so every reduction is deterministic.
+// wavefront + block tree; the per-block partials are summed in a fixed order
+// by the blocks of the next kernel (or a finalising block where they are too
+// many for that), so every reduction is deterministic.
 //
 // Solvers:
 //   * Jacobi-preconditioned CG (FP64, or FP32 vectors with FP64 dots);
