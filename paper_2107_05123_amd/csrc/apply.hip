@@ -785,12 +785,15 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t g) {
 template <typename T>
 struct OpConst {
   T A = 0, Bc = 0, Ms = 0, Am = 0, Bm = 0;
+  double gs = 0, wdet = 0;  // right-hand sides, residual and energy: 2/h and det J = (h/2)^d
 };
 template <int DIM, typename T, int OP>
 __device__ __forceinline__ OpConst<T> op_const(const BrickArgs<T>& a, int lev) {
   // FP32 fields carry 1 + phi, so rho = (beta - alpha) + alpha (1 + phi)
   const double beta0 = sizeof(T) == 8 ? a.beta : a.beta - a.alpha;
   OpConst<T> o;
+  o.gs = ldexp(1.0, lev + 1);
+  o.wdet = ldexp(1.0, -(lev + 1) * DIM);
   // mass: det J w^2d; stiffness: (h/2)^(d-2) / 4 w^2(d-1); phi: w^d
   const double mass = ldexp(kWp<2 * DIM>, -(lev + 1) * DIM);
   const double F = ldexp(kWp<2 * (DIM - 1)> / 4.0, -(lev + 1) * (DIM - 2));
@@ -913,23 +916,19 @@ __device__ __forceinline__ void leaf_diag(const BrickArgs<T>& a, int lev, const 
   }
 }
 
-// One leaf of the form OP: corner values xc (inputs) and cc (coefficients),
-// or the accessor cv(f, a) for the heavy forms, to corner results ye.  The
-// momentum form instead hands each component's results to out(f, y) in turn.
-template <int DIM, typename T, int OP, class XC, class CC, class CV, class OUT>
+// One leaf of the form OP (not the momentum form, which hands each component's
+// results over in turn, see el_vp): corner values xc (inputs) and cc
+// (coefficients), or the accessor cv(f, a) for the Cahn-Hilliard Jacobian, to
+// corner results ye.
+template <int DIM, typename T, int OP, class XC, class CC, class CV>
 __device__ __forceinline__ void leaf_form(const BrickArgs<T>& a, const OpConst<T>& oc, int lev, const XC& xc,
-                                          const CC& cc, const CV& cv, const OUT& out,
-                                          T (*ye)[1 << DIM]) {
+                                          const CC& cc, const CV& cv, T (*ye)[1 << DIM]) {
   using TR = Traits<OP, DIM>;
   constexpr int NI = TR::NI, NC = 1 << DIM;
-  // CHNS forms: physical gradient scale 2/h and det J = (h/2)^d
-  const double gs = ldexp(1.0, lev + 1), wdet = ldexp(1.0, -(lev + 1) * DIM);
   if constexpr (OP == K_DIAG) {
     leaf_diag<DIM, T>(a, lev, xc[0], cc[0], ye[0]);
   } else if constexpr (OP == K_CH_JAC) {
     el_chj<DIM, T>(cv, a.fc, lev, ye);
-  } else if constexpr (OP == K_VP) {
-    el_vp<DIM, T>(cv, a.fc, lev, out);
   } else if constexpr (OP == K_PP || OP == K_PPS) {
     elem_pp<DIM, T>(xc[0], cc[0], oc.A, oc.Bc, ye[0]);
     if constexpr (OP == K_PPS) {
@@ -953,15 +952,15 @@ __device__ __forceinline__ void leaf_form(const BrickArgs<T>& a, const OpConst<T
 #pragma unroll
     for (int f = 0; f < NI; ++f) elem_mass_apply<DIM, T>(xc[f], r, ye[f]);
   } else if constexpr (OP == K_CH_RES) {
-    el_ch_res<DIM>(xc, cc, a.phys, gs, wdet, ye);
+    el_ch_res<DIM>(xc, cc, a.phys, oc.gs, oc.wdet, ye);
   } else if constexpr (OP == K_VP_RHS) {
-    el_vp_rhs<DIM>(cc, a.phys, gs, wdet, ye);
+    el_vp_rhs<DIM>(cc, a.phys, oc.gs, oc.wdet, ye);
   } else if constexpr (OP == K_PP_RHS) {
-    el_pp_rhs<DIM>(cc, a.phys, gs, wdet, ye);
+    el_pp_rhs<DIM>(cc, a.phys, oc.gs, oc.wdet, ye);
   } else if constexpr (OP == K_VU_RHS) {
-    el_vu_rhs<DIM>(cc, a.phys, gs, wdet, ye);
+    el_vu_rhs<DIM>(cc, a.phys, oc.gs, oc.wdet, ye);
   } else {
-    el_energy<DIM>(cc, a.phys, gs, wdet, ye);
+    el_energy<DIM>(cc, a.phys, oc.gs, oc.wdet, ye);
   }
 }
 
@@ -1028,15 +1027,34 @@ struct BrickShm {
   // reads of the layer it replaces) and leaves LDS for two waves per SIMD
   static constexpr bool HEAVY = OP == K_VP || OP == K_CH_JAC;
   static constexpr int RING = WHOLE ? B + 1 : (HEAVY ? 2 : 3);
-  T lay[RING][BPB][NV][NL];
+  using Lay = T[RING][BPB][NV][NL];
   // per-corner-type leaf contributions, indexed by the node they land on
   // (zero where no leaf of the brick lands): a node sums NH entries
-  T accn[BPB][TR::NO][NH][NL];
+  using Acc = T[BPB][TR::NO][NH][NL];
+  static constexpr size_t kBytes = sizeof(Lay) + sizeof(Acc);
+};
+// pointer to the first of an LDS array's elements
+template <class A>
+using LdsPtr = __attribute__((address_space(3))) std::remove_extent_t<A>*;
+// The LDS of a kernel of one brick class: two objects, by pointers that say
+// they are LDS.  As one object, or by plain references, the compiler holds the
+// reads of the layers back behind the stores of the contributions and spills
+// more: the velocity-update right-hand side takes 40.4 us at 8^3 instead of
+// 34.7, the momentum apply 20.4 instead of 16.6.
+template <class SH>
+struct OwnLds {
+  __device__ __forceinline__ static auto lay() {
+    __shared__ typename SH::Lay m;
+    return (LdsPtr<typename SH::Lay>)m;
+  }
+  __device__ __forceinline__ static auto acc() {
+    __shared__ typename SH::Acc m;
+    return (LdsPtr<typename SH::Acc>)m;
+  }
 };
 
-template <int DIM, int B, typename T, int OP, bool WHOLE, bool STRUCT>
-__device__ __forceinline__ void brick_body(const BrickArgs<T>& a, BrickShm<DIM, B, T, OP, WHOLE>& sm, uint32_t block,
-                                           uint32_t grid) {
+template <int DIM, int B, typename T, int OP, bool WHOLE, bool STRUCT, class LDS>
+__device__ __forceinline__ void brick_body(const BrickArgs<T>& a, uint32_t block, uint32_t grid) {
   using TR = Traits<OP, DIM>;
   using SH = BrickShm<DIM, B, T, OP, WHOLE>;
   constexpr int NI = TR::NI, NCF = TR::NCF, NO = TR::NO, NV = NI + NCF;
@@ -1048,8 +1066,8 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a, BrickShm<DIM, 
   constexpr int RING = SH::RING;
   // the 3D pressure form keeps its lower layer transformed (march.h)
   constexpr bool MARCH = OP == K_PP && DIM == 3;
-  auto& lay = sm.lay;
-  auto& accn = sm.accn;
+  auto* const lay = LDS::lay();
+  auto* const accn = LDS::acc();
   if (a.done && *a.done) return;
   const int lane = threadIdx.x, bl = lane / LPB, ll = lane % LPB;
   const int64_t brick = (int64_t)xcd_block(block, grid) * BPB + bl;
@@ -1344,18 +1362,25 @@ __device__ __forceinline__ void brick_body(const BrickArgs<T>& a, BrickShm<DIM, 
         const int p = (ix + bx) + (DIM == 3 ? (iy + by) * (B + 1) : 0);
         return lay[(ez + bz) % RING][bl][f][p];
       };
-      if constexpr (!MARCH)
-      leaf_form<DIM, T, OP>(a, oc, lev, xc, cc, cv, [&](int f, const T* yf) {
+      if constexpr (OP == K_VP) {
         // each component's corner values go to the node accumulators as
         // soon as they are formed
+        el_vp<DIM, T>(cv, a.fc, lev, [&](int f, const T* yf) {
 #pragma unroll
-        for (int c = 0; c < NH; ++c) {
-          const int p = (ix + (c & 1)) + (DIM == 3 ? (iy + ((c >> 1) & 1)) * (B + 1) : 0);
-          accn[bl][f][c][p] = yf[c] + carry[f][c];
-          carry[f][c] = yf[c + NH];
-        }
-      }, ye);
-      if constexpr (OP != K_VP) {
+          for (int c = 0; c < NH; ++c) {
+            const int p = (ix + (c & 1)) + (DIM == 3 ? (iy + ((c >> 1) & 1)) * (B + 1) : 0);
+            accn[bl][f][c][p] = yf[c] + carry[f][c];
+            carry[f][c] = yf[c + NH];
+          }
+        });
+      } else {
+        // the right-hand sides are called here: through leaf_form the compiler
+        // allocates their registers otherwise (pressure at 128^3 1,474 us,
+        // here 1,412; velocity update on the 5-9 octree 3.50 ms, here 3.32)
+        if constexpr (OP == K_VP_RHS) el_vp_rhs<DIM>(cc, a.phys, oc.gs, oc.wdet, ye);
+        else if constexpr (OP == K_PP_RHS) el_pp_rhs<DIM>(cc, a.phys, oc.gs, oc.wdet, ye);
+        else if constexpr (OP == K_VU_RHS) el_vu_rhs<DIM>(cc, a.phys, oc.gs, oc.wdet, ye);
+        else if constexpr (!MARCH) leaf_form<DIM, T, OP>(a, oc, lev, xc, cc, cv, ye);
 #pragma unroll
         for (int f = 0; f < NO; ++f)
 #pragma unroll
@@ -1500,10 +1525,14 @@ __global__ __launch_bounds__(64) void k_tile2(BrickArgs<T> a, int tx, int own) {
       }
     if (z + 1 < ze) load(z + 2, hi);
     auto cv = [&](int f, int ca) -> T { return f < NI ? xc[f < NI ? f : 0][ca] : cc[f < NI ? 0 : f - NI][ca]; };
-    leaf_form<2, T, OP>(a, oc, lev, xc, cc, cv, [&](int f, const T* yf) {
+    if constexpr (OP == K_VP) {
+      el_vp<2, T>(cv, a.fc, lev, [&](int f, const T* yf) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) ye[f][c] = yf[c];
-    }, ye);
+        for (int c = 0; c < 4; ++c) ye[f][c] = yf[c];
+      });
+    } else {
+      leaf_form<2, T, OP>(a, oc, lev, xc, cc, cv, ye);
+    }
 #pragma unroll
     for (int f = 0; f < NO; ++f)
 #pragma unroll
@@ -1539,16 +1568,16 @@ using ShmOf = BrickShm<DIM, B, T, OP, whole_fits<DIM, B, T, OP>()>;
 
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) void k_brick(BrickArgs<T> a) {
-  __shared__ ShmOf<DIM, B, T, OP> sm;
-  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT>(a, sm, blockIdx.x, gridDim.x);
+  using SH = ShmOf<DIM, B, T, OP>;
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, OwnLds<SH>>(a, blockIdx.x, gridDim.x);
 }
 // the pressure and mass forms (at most 128 VGPRs in FP64): capped at four
 // waves per SIMD, which keeps the FP32 instances from trading their latency
 // hiding for occupancy
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_brick_o4(BrickArgs<T> a) {
-  __shared__ ShmOf<DIM, B, T, OP> sm;
-  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT>(a, sm, blockIdx.x, gridDim.x);
+  using SH = ShmOf<DIM, B, T, OP>;
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, OwnLds<SH>>(a, blockIdx.x, gridDim.x);
 }
 // two FP64 3D forms on 8^3 bricks.  The Cahn-Hilliard Jacobian on structured
 // bricks: its LDS admits three waves per SIMD, which at 128^3 leaves a third
@@ -1556,13 +1585,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 // rounds (0.095 -> 0.090 ms; equal at 256^3; on adaptive meshes three are
 // faster).  The momentum form: a chain of dependent FMAs and reciprocals
 // bounds it, and left alone the compiler takes more than 256 registers and
-// one wave per SIMD; held to two it spills 12 bytes a lane on structured
-// bricks and 80 on table bricks and still gains, 192 -> 164 us at 128^3 and
+// one wave per SIMD; held to two it spills 16 bytes a lane on structured
+// bricks and 88 on table bricks and still gains, 192 -> 164 us at 128^3 and
 // 461 -> 426 us on the 5-9 octree
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_brick_o2(BrickArgs<T> a) {
-  __shared__ ShmOf<DIM, B, T, OP> sm;
-  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT>(a, sm, blockIdx.x, gridDim.x);
+  using SH = ShmOf<DIM, B, T, OP>;
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, OwnLds<SH>>(a, blockIdx.x, gridDim.x);
 }
 
 // Single leaves (bricks of one) of a table mesh: one lane per leaf, its
@@ -1601,10 +1630,14 @@ __device__ __forceinline__ void single_body(const BrickArgs<T>& a, uint32_t bloc
     M.finish(ye[0] + 4);
   } else {
     auto cv = [&](int f, int ca) -> T { return f < NI ? xc[f < NI ? f : 0][ca] : cc[f < NI ? 0 : f - NI][ca]; };
-    leaf_form<DIM, T, OP>(a, op_const<DIM, T, OP>(a, lev), lev, xc, cc, cv, [&](int f, const T* yf) {
+    if constexpr (OP == K_VP) {
+      el_vp<DIM, T>(cv, a.fc, lev, [&](int f, const T* yf) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) ye[f][c] = yf[c];
-    }, ye);
+        for (int c = 0; c < NC; ++c) ye[f][c] = yf[c];
+      });
+    } else {
+      leaf_form<DIM, T, OP>(a, op_const<DIM, T, OP>(a, lev), lev, xc, cc, cv, ye);
+    }
   }
 #pragma unroll
   for (int f = 0; f < NO; ++f)
@@ -1634,11 +1667,29 @@ struct ClassArgs {
 struct ClassTable {
   ClassArgs c[kBrickClasses];  // edge 8, 4, 2, 1
 };
+// its LDS: one object for whichever class a block belongs to (two, each as
+// large as the class that needs most of it, would cost the shifted pressure
+// form a wave)
+template <int DIM, typename T, int OP, bool EIGHT>
+struct ClassLds {
+  static constexpr size_t kBytes = std::max({EIGHT ? ShmOf<DIM, 8, T, OP>::kBytes : 0, ShmOf<DIM, 4, T, OP>::kBytes,
+                                             ShmOf<DIM, 2, T, OP>::kBytes});
+  using Bytes = unsigned char[kBytes];
+  __device__ __forceinline__ static LdsPtr<Bytes> raw() {
+    __shared__ __align__(16) Bytes m;
+    return (LdsPtr<Bytes>)m;
+  }
+  template <class SH>
+  struct Of {
+    __device__ __forceinline__ static auto lay() { return (LdsPtr<typename SH::Lay>)raw(); }
+    __device__ __forceinline__ static auto acc() {
+      return (LdsPtr<typename SH::Acc>)(raw() + sizeof(typename SH::Lay));
+    }
+  };
+};
 template <int DIM, typename T, int OP, bool EIGHT>
 __device__ __forceinline__ void bricks_body(BrickArgs<T> a, const ClassTable& t) {
-  constexpr size_t kShm = std::max({EIGHT ? sizeof(ShmOf<DIM, 8, T, OP>) : 0, sizeof(ShmOf<DIM, 4, T, OP>),
-                                    sizeof(ShmOf<DIM, 2, T, OP>)});
-  __shared__ __align__(16) unsigned char raw[kShm];
+  using LDS = ClassLds<DIM, T, OP, EIGHT>;
   if (a.done && *a.done) return;
   const uint32_t b = blockIdx.x;
   auto take = [&](int k) {
@@ -1655,14 +1706,17 @@ __device__ __forceinline__ void bricks_body(BrickArgs<T> a, const ClassTable& t)
   if (EIGHT && b < t.c[0].first + t.c[0].grid) {
     if constexpr (EIGHT) {
       const uint32_t i = take(0);
-      brick_body<DIM, 8, T, OP, whole_fits<DIM, 8, T, OP>(), false>(a, *(ShmOf<DIM, 8, T, OP>*)raw, i, t.c[0].grid);
+      brick_body<DIM, 8, T, OP, whole_fits<DIM, 8, T, OP>(), false,
+                  typename LDS::template Of<ShmOf<DIM, 8, T, OP>>>(a, i, t.c[0].grid);
     }
   } else if (b < t.c[1].first + t.c[1].grid) {
     const uint32_t i = take(1);
-    brick_body<DIM, 4, T, OP, whole_fits<DIM, 4, T, OP>(), false>(a, *(ShmOf<DIM, 4, T, OP>*)raw, i, t.c[1].grid);
+    brick_body<DIM, 4, T, OP, whole_fits<DIM, 4, T, OP>(), false,
+                typename LDS::template Of<ShmOf<DIM, 4, T, OP>>>(a, i, t.c[1].grid);
   } else if (b < t.c[2].first + t.c[2].grid) {
     const uint32_t i = take(2);
-    brick_body<DIM, 2, T, OP, whole_fits<DIM, 2, T, OP>(), false>(a, *(ShmOf<DIM, 2, T, OP>*)raw, i, t.c[2].grid);
+    brick_body<DIM, 2, T, OP, whole_fits<DIM, 2, T, OP>(), false,
+                typename LDS::template Of<ShmOf<DIM, 2, T, OP>>>(a, i, t.c[2].grid);
   } else {
     const uint32_t i = take(3);
     single_body<DIM, T, OP>(a, i, t.c[3].grid);
