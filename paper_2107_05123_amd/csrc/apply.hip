@@ -1948,7 +1948,13 @@ template <int OP>
 constexpr bool eight_merged() {
   return OP == K_PP || OP == K_PPS || OP == K_VPS || OP == K_MASS || OP == K_DIAG;
 }
-// blocks that launch_bricks starts
+// the right-hand sides: every register of a SIMD, so one wave on each of the
+// 1,024
+template <int OP>
+constexpr bool is_rhs() {
+  return OP == K_VP_RHS || OP == K_PP_RHS || OP == K_VU_RHS;
+}
+// blocks that launch_bricks starts (the right-hand sides have no fused dot)
 template <int DIM, int OP>
 int64_t brick_blocks(const DevMesh& dm) {
   int64_t n = 0;
@@ -1963,6 +1969,15 @@ int64_t brick_blocks(const DevMesh& dm) {
 template <int DIM, typename T, int OP>
 int launch_bricks(const DevMesh& dm, BrickArgs<T> a, hipStream_t s, int& part_off) {
   constexpr bool EIGHT = eight_merged<OP>();
+  // The 3D right-hand sides, of which the merged kernel holds two waves on a CU
+  // (its LDS is that of sixteen 2^3 bricks): 4^3 bricks with a wave for every
+  // SIMD run in a kernel of their own (1,827 us against 1,946 for the
+  // prediction on the 5-9 octree; with fewer, one launch is faster: 105 us
+  // against 139 at levels 4-7), and so do single leaves with no other class
+  // beside them (pressure 41.4 us against 45.2 at levels 2-4).
+  constexpr bool RHS3 = is_rhs<OP>() && DIM == 3;
+  int classes = 0;
+  for (const DevBrickClass& bc : dm.cls) classes += bc.count > 0;
   ClassTable t{};
   uint32_t end = 0;
   double* part = a.partials ? a.partials + part_off : nullptr;
@@ -1975,12 +1990,18 @@ int launch_bricks(const DevMesh& dm, BrickArgs<T> a, hipStream_t s, int& part_of
     a.count = bc.count;
     a.slot_base = bc.slot_base;
     a.nbnd = bc.nbnd;
-    if (dm.structured || (!EIGHT && bc.B == 8)) {
+    const bool alone =
+        (!EIGHT && bc.B == 8) || (RHS3 && ((bc.B == 4 && grid >= 1024) || (bc.B == 1 && classes == 1)));
+    if (dm.structured || alone) {
       if (!grid) continue;
       a.anchor = bc.anchor;
       a.partials = part;
       if constexpr (!EIGHT) {
-        if (!dm.structured) launch_one<DIM, 8, T, OP, false>(grid, s, a);
+        if (!dm.structured && bc.B == 8) launch_one<DIM, 8, T, OP, false>(grid, s, a);
+      }
+      if constexpr (RHS3) {
+        if (!dm.structured && bc.B == 4) launch_one<DIM, 4, T, OP, false>(grid, s, a);
+        if (!dm.structured && bc.B == 1) launch_one<DIM, 1, T, OP, false>(grid, s, a);
       }
       if constexpr (DIM == 3 && !(OP == K_PP && sizeof(T) == 8) && OP != K_DIAG)
         if (dm.structured) launch_structured<T, OP>(bc.B, grid, s, a);
