@@ -1886,15 +1886,37 @@ __global__ void k_take_block(double* blk, const double* y, const uint8_t* color,
 // long chunks do less work and short ones fill the chip; `fill` blocks are
 // enough (measured minimum of the chunk sweeps at 16 to 256 leaves per edge
 // in 3D, where chunks below three layers only pay while the chip is not full).
-int chunk_own(int64_t tiles, int side, int64_t fill, int least) {
-  if (tiles * (side + 1) <= fill / 3) return 1;
+// Chunks of one row or layer as long as there are at most `one` of them.
+int chunk_own(int64_t tiles, int side, int64_t fill, int64_t one, int least) {
+  if (tiles * (side + 1) <= one) return 1;
   return (int)std::max<int64_t>(least, (tiles * (side + 1) + fill - 1) / fill);
 }
 
 int64_t tile3_columns(int side) {
   return (int64_t)((side + kTileX - 1) / kTileX) * ((side + kTileY - 1) / kTileY);
 }
-int tile3_own(int side) { return chunk_own(tile3_columns(side), side, 1536, 3); }
+int tile3_own(int side) { return chunk_own(tile3_columns(side), side, 1536, 512, 3); }
+// the right-hand sides: every register of a SIMD, so one wave on each of the
+// 1,024
+template <int OP>
+constexpr bool is_rhs() {
+  return OP == K_VP_RHS || OP == K_PP_RHS || OP == K_VU_RHS;
+}
+// 2D: a right-hand side has room for 1,024 blocks at once, and more would run
+// in a second round (the pressure's at 256^2 leaves 21.1 -> 16.3 us, at 1024^2
+// 110 -> 89, as much as the bricks took)
+template <int OP>
+int tile2_own(int tiles, int side) {
+  return is_rhs<OP>() ? chunk_own(tiles, side, 1024, 1024, 2) : chunk_own(tiles, side, 6144, 2048, 2);
+}
+// ... and on at most 32^2 leaves stays on the bricks: there a wave's two leaf
+// rows take longer than one leaf of a brick and the combine (10.3 us against
+// 8.4 at 8^2 and 10.4 against 9.4 at 32^2 for the pressure's, 10.4 against 14.0
+// at 64^2)
+template <int DIM, int OP>
+bool rhs_on_bricks(int side) {
+  return DIM == 2 && is_rhs<OP>() && side <= 32;
+}
 // 3D pressure operator on a uniform mesh: arguments of k_pp_tile
 template <typename T>
 TileArgs<T> tile3_args(const BrickArgs<T>& b, int level, int own) {
@@ -1926,14 +1948,14 @@ void launch_one(int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
   else k_brick<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
 }
 
-// uniform 3D meshes: one brick class, node numbers computed
-template <typename T, int OP>
+// uniform meshes: one brick class, node numbers computed
+template <int DIM, typename T, int OP>
 void launch_structured(int B, int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
   switch (B) {
-    case 8: launch_one<3, 8, T, OP, true>(grid, s, a); break;
-    case 4: launch_one<3, 4, T, OP, true>(grid, s, a); break;
-    case 2: launch_one<3, 2, T, OP, true>(grid, s, a); break;
-    default: launch_one<3, 1, T, OP, true>(grid, s, a); break;
+    case 8: launch_one<DIM, 8, T, OP, true>(grid, s, a); break;
+    case 4: launch_one<DIM, 4, T, OP, true>(grid, s, a); break;
+    case 2: launch_one<DIM, 2, T, OP, true>(grid, s, a); break;
+    default: launch_one<DIM, 1, T, OP, true>(grid, s, a); break;
   }
 }
 
@@ -1947,12 +1969,6 @@ int64_t class_blocks(const DevBrickClass& bc, int dim) {
 template <int OP>
 constexpr bool eight_merged() {
   return OP == K_PP || OP == K_PPS || OP == K_VPS || OP == K_MASS || OP == K_DIAG;
-}
-// the right-hand sides: every register of a SIMD, so one wave on each of the
-// 1,024
-template <int OP>
-constexpr bool is_rhs() {
-  return OP == K_VP_RHS || OP == K_PP_RHS || OP == K_VU_RHS;
 }
 // blocks that launch_bricks starts (the right-hand sides have no fused dot)
 template <int DIM, int OP>
@@ -2003,8 +2019,8 @@ int launch_bricks(const DevMesh& dm, BrickArgs<T> a, hipStream_t s, int& part_of
         if (!dm.structured && bc.B == 4) launch_one<DIM, 4, T, OP, false>(grid, s, a);
         if (!dm.structured && bc.B == 1) launch_one<DIM, 1, T, OP, false>(grid, s, a);
       }
-      if constexpr (DIM == 3 && !(OP == K_PP && sizeof(T) == 8) && OP != K_DIAG)
-        if (dm.structured) launch_structured<T, OP>(bc.B, grid, s, a);
+      if constexpr (DIM == 3 ? !(OP == K_PP && sizeof(T) == 8) && OP != K_DIAG : is_rhs<OP>())
+        if (dm.structured) launch_structured<DIM, T, OP>(bc.B, grid, s, a);
       CHNS_HIP(hipGetLastError());
       if (part) {
         part += grid;
@@ -2107,16 +2123,17 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   int part_off = 0;
   const char* tag = op_tag(OP, sizeof(T) == 8);
   hipEvent_t ev;
-  // uniform meshes in one kernel, no slots and no combine: every 2D form and
-  // the 3D pressure operator in FP64.  In FP32 that operator keeps the bricks
-  // and their order of sums, so that it gives the same bits as the brick path
-  // of an octree with the same leaves: refinement around restarted FP32 solves
-  // turns a change of rounding into a few iterations (327 to 338 for the
-  // learned preconditioner at 128^3), and the two paths agree exactly.
+  // uniform meshes in one kernel, no slots and no combine: every 2D form (the
+  // right-hand sides from 64^2 leaves) and the 3D pressure operator in FP64.
+  // In FP32 that operator keeps the bricks and their order of sums, so that it
+  // gives the same bits as the brick path of an octree with the same leaves:
+  // refinement around restarted FP32 solves turns a change of rounding into a
+  // few iterations (327 to 338 for the learned preconditioner at 128^3), and
+  // the two paths agree exactly.
   constexpr bool TILE3 = DIM == 3 && OP == K_PP && sizeof(T) == 8;
-  const bool whole = dm.structured && (DIM == 2 || TILE3) && OP != K_DIAG;
+  const bool whole = dm.structured && (DIM == 2 || TILE3) && OP != K_DIAG && !rhs_on_bricks<DIM, OP>(dm.side);
   const int tx2 = std::max(1, (dm.side - 1 + kTile2X - 1) / kTile2X);
-  const int own = !whole ? 1 : DIM == 2 ? chunk_own(tx2, dm.side, 6144, 2) : tile3_own(dm.side);
+  const int own = !whole ? 1 : DIM == 2 ? tile2_own<OP>(tx2, dm.side) : tile3_own(dm.side);
   const int64_t cb = whole ? 0 : combine_blocks(dm);
   const int64_t total = !whole ? brick_blocks<DIM, OP>(dm) + cb
                                : (DIM == 2 ? tx2 : tile3_columns(dm.side)) * (int64_t)((dm.side + own) / own);
