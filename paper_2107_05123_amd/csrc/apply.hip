@@ -1571,9 +1571,11 @@ __global__ __launch_bounds__(64) void k_brick(BrickArgs<T> a) {
   using SH = ShmOf<DIM, B, T, OP>;
   brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, OwnLds<SH>>(a, blockIdx.x, gridDim.x);
 }
-// the pressure and mass forms (at most 128 VGPRs in FP64): capped at four
-// waves per SIMD, which keeps the FP32 instances from trading their latency
-// hiding for occupancy
+// the pressure forms (at most 128 VGPRs in FP64): capped at four waves per
+// SIMD, which keeps the FP32 instances from trading their latency hiding for
+// occupancy.  The mass form on uniform meshes (60 VGPRs) is bound by memory and
+// runs uncapped: apply at 256^3 187 us FP64 and 135 FP32, against 224 and 162
+// with the cap (equal at 128^3)
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_brick_o4(BrickArgs<T> a) {
   using SH = ShmOf<DIM, B, T, OP>;
@@ -1942,7 +1944,7 @@ void launch_one(int64_t grid, hipStream_t s, const BrickArgs<T>& a) {
   // the scalar momentum form (viscous stiffness and density mass together)
   // needs ~130 registers: capped at four waves it spilled (88 bytes per lane
   // on table bricks), uncapped it runs three without
-  if constexpr (OP == K_PP || OP == K_PPS || OP == K_MASS) k_brick_o4<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
+  if constexpr (OP == K_PP || OP == K_PPS) k_brick_o4<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
   else if constexpr (((OP == K_CH_JAC && STRUCT) || OP == K_VP) && DIM == 3 && B == 8 && sizeof(T) == 8)
     k_brick_o2<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
   else k_brick<DIM, B, T, OP, STRUCT><<<g, blk, 0, s>>>(a);
