@@ -1033,16 +1033,17 @@ struct BrickShm {
   using Acc = T[BPB][TR::NO][NH][NL];
   static constexpr size_t kBytes = sizeof(Lay) + sizeof(Acc);
 };
-// pointer to the first of an LDS array's elements
+// Pointer to the first of an LDS array's elements.  The bricks reach their LDS
+// by pointers that say it is LDS: by plain references, kept in the closures of
+// the body's lambdas, the compiler holds the reads of the layers back behind
+// the stores of the contributions and spills more (velocity-update right-hand
+// side at 8^3 40.4 us against 35.5, momentum apply 20.4 against 16.1).
 template <class A>
 using LdsPtr = __attribute__((address_space(3))) std::remove_extent_t<A>*;
-// The LDS of a kernel of one brick class: two objects, by pointers that say
-// they are LDS.  As one object, or by plain references, the compiler holds the
-// reads of the layers back behind the stores of the contributions and spills
-// more: the velocity-update right-hand side takes 40.4 us at 8^3 instead of
-// 34.7, the momentum apply 20.4 instead of 16.6.
+// two objects: registers for a third wave of the Cahn-Hilliard Jacobian on
+// table bricks
 template <class SH>
-struct OwnLds {
+struct TwoLds {
   __device__ __forceinline__ static auto lay() {
     __shared__ typename SH::Lay m;
     return (LdsPtr<typename SH::Lay>)m;
@@ -1050,6 +1051,24 @@ struct OwnLds {
   __device__ __forceinline__ static auto acc() {
     __shared__ typename SH::Acc m;
     return (LdsPtr<typename SH::Acc>)m;
+  }
+};
+// one object of N bytes: for the momentum form on 8^3 bricks, which spills 8
+// bytes a lane less so (437 us against 432 on the 6-9 octree), and for the
+// kernels that run whichever class a block belongs to (two objects, each as
+// large as the class that needs most of it, would cost the shifted pressure
+// form a wave)
+template <size_t N>
+__device__ __forceinline__ auto lds_bytes() {
+  using Bytes = unsigned char[N];
+  __shared__ __align__(16) Bytes m;
+  return (LdsPtr<Bytes>)m;
+}
+template <class SH, size_t N = SH::kBytes>
+struct OneLds {
+  __device__ __forceinline__ static auto lay() { return (LdsPtr<typename SH::Lay>)lds_bytes<N>(); }
+  __device__ __forceinline__ static auto acc() {
+    return (LdsPtr<typename SH::Acc>)(lds_bytes<N>() + sizeof(typename SH::Lay));
   }
 };
 
@@ -1569,7 +1588,7 @@ using ShmOf = BrickShm<DIM, B, T, OP, whole_fits<DIM, B, T, OP>()>;
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) void k_brick(BrickArgs<T> a) {
   using SH = ShmOf<DIM, B, T, OP>;
-  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, OwnLds<SH>>(a, blockIdx.x, gridDim.x);
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, TwoLds<SH>>(a, blockIdx.x, gridDim.x);
 }
 // the pressure forms (at most 128 VGPRs in FP64): capped at four waves per
 // SIMD, which keeps the FP32 instances from trading their latency hiding for
@@ -1579,7 +1598,7 @@ __global__ __launch_bounds__(64) void k_brick(BrickArgs<T> a) {
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_brick_o4(BrickArgs<T> a) {
   using SH = ShmOf<DIM, B, T, OP>;
-  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, OwnLds<SH>>(a, blockIdx.x, gridDim.x);
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, TwoLds<SH>>(a, blockIdx.x, gridDim.x);
 }
 // two FP64 3D forms on 8^3 bricks.  The Cahn-Hilliard Jacobian on structured
 // bricks: its LDS admits three waves per SIMD, which at 128^3 leaves a third
@@ -1587,13 +1606,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 // rounds (0.095 -> 0.090 ms; equal at 256^3; on adaptive meshes three are
 // faster).  The momentum form: a chain of dependent FMAs and reciprocals
 // bounds it, and left alone the compiler takes more than 256 registers and
-// one wave per SIMD; held to two it spills 16 bytes a lane on structured
-// bricks and 88 on table bricks and still gains, 192 -> 164 us at 128^3 and
+// one wave per SIMD; held to two it spills 8 bytes a lane on structured
+// bricks and 84 on table bricks and still gains, 192 -> 164 us at 128^3 and
 // 461 -> 426 us on the 5-9 octree
 template <int DIM, int B, typename T, int OP, bool STRUCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_brick_o2(BrickArgs<T> a) {
   using SH = ShmOf<DIM, B, T, OP>;
-  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, OwnLds<SH>>(a, blockIdx.x, gridDim.x);
+  using LDS = std::conditional_t<OP == K_VP, OneLds<SH>, TwoLds<SH>>;
+  brick_body<DIM, B, T, OP, whole_fits<DIM, B, T, OP>(), STRUCT, LDS>(a, blockIdx.x, gridDim.x);
 }
 
 // Single leaves (bricks of one) of a table mesh: one lane per leaf, its
@@ -1669,29 +1689,10 @@ struct ClassArgs {
 struct ClassTable {
   ClassArgs c[kBrickClasses];  // edge 8, 4, 2, 1
 };
-// its LDS: one object for whichever class a block belongs to (two, each as
-// large as the class that needs most of it, would cost the shifted pressure
-// form a wave)
-template <int DIM, typename T, int OP, bool EIGHT>
-struct ClassLds {
-  static constexpr size_t kBytes = std::max({EIGHT ? ShmOf<DIM, 8, T, OP>::kBytes : 0, ShmOf<DIM, 4, T, OP>::kBytes,
-                                             ShmOf<DIM, 2, T, OP>::kBytes});
-  using Bytes = unsigned char[kBytes];
-  __device__ __forceinline__ static LdsPtr<Bytes> raw() {
-    __shared__ __align__(16) Bytes m;
-    return (LdsPtr<Bytes>)m;
-  }
-  template <class SH>
-  struct Of {
-    __device__ __forceinline__ static auto lay() { return (LdsPtr<typename SH::Lay>)raw(); }
-    __device__ __forceinline__ static auto acc() {
-      return (LdsPtr<typename SH::Acc>)(raw() + sizeof(typename SH::Lay));
-    }
-  };
-};
 template <int DIM, typename T, int OP, bool EIGHT>
 __device__ __forceinline__ void bricks_body(BrickArgs<T> a, const ClassTable& t) {
-  using LDS = ClassLds<DIM, T, OP, EIGHT>;
+  constexpr size_t kShm = std::max({EIGHT ? ShmOf<DIM, 8, T, OP>::kBytes : 0, ShmOf<DIM, 4, T, OP>::kBytes,
+                                    ShmOf<DIM, 2, T, OP>::kBytes});
   if (a.done && *a.done) return;
   const uint32_t b = blockIdx.x;
   auto take = [&](int k) {
@@ -1709,16 +1710,16 @@ __device__ __forceinline__ void bricks_body(BrickArgs<T> a, const ClassTable& t)
     if constexpr (EIGHT) {
       const uint32_t i = take(0);
       brick_body<DIM, 8, T, OP, whole_fits<DIM, 8, T, OP>(), false,
-                  typename LDS::template Of<ShmOf<DIM, 8, T, OP>>>(a, i, t.c[0].grid);
+                  OneLds<ShmOf<DIM, 8, T, OP>, kShm>>(a, i, t.c[0].grid);
     }
   } else if (b < t.c[1].first + t.c[1].grid) {
     const uint32_t i = take(1);
     brick_body<DIM, 4, T, OP, whole_fits<DIM, 4, T, OP>(), false,
-                typename LDS::template Of<ShmOf<DIM, 4, T, OP>>>(a, i, t.c[1].grid);
+                OneLds<ShmOf<DIM, 4, T, OP>, kShm>>(a, i, t.c[1].grid);
   } else if (b < t.c[2].first + t.c[2].grid) {
     const uint32_t i = take(2);
     brick_body<DIM, 2, T, OP, whole_fits<DIM, 2, T, OP>(), false,
-                typename LDS::template Of<ShmOf<DIM, 2, T, OP>>>(a, i, t.c[2].grid);
+                OneLds<ShmOf<DIM, 2, T, OP>, kShm>>(a, i, t.c[2].grid);
   } else {
     const uint32_t i = take(3);
     single_body<DIM, T, OP>(a, i, t.c[3].grid);
