@@ -43,6 +43,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kLayers = 14;
 constexpr int kInCh = 8;
 constexpr int kCh[4] = {16, 32, 48, 64};
+constexpr int kLevel[kLayers] = {0, 0, 1, 1, 2, 2, 3, 3, 2, 2, 1, 1, 0, 0};  // a layer runs on edge E >> level
 
 struct ULayer {
   int ci = 0, co = 0;
@@ -62,6 +63,7 @@ struct UActs {
            *dcat1 = nullptr, *dA9 = nullptr, *dA8 = nullptr, *dcat2 = nullptr, *dA7 = nullptr, *dA6 = nullptr,
            *dP2 = nullptr, *dA4 = nullptr, *dP1 = nullptr, *dA2 = nullptr, *dP0 = nullptr, *dA0 = nullptr;
   float *out = nullptr, *target = nullptr, *mask = nullptr, *dout = nullptr;
+  float* partial = nullptr;  // weight-gradient sums of the splits
 };
 
 struct UNet {
@@ -78,8 +80,6 @@ struct UNet {
   int step = 0;
   bool ready = false;
   std::vector<UActs> acts;
-  float* partial = nullptr;
-  size_t partial_cap = 0;
   double* red = nullptr;      // reduction partials (device)
   double* scal = nullptr;     // device scalars: [0] rms, [1] mean, [2] loss or beta, [3] count,
                               // [4..7] A-norm objective, [8] n.A n, [9] g.n
@@ -1135,16 +1135,18 @@ int conv(const uint16_t* in, int cs_in, int ci, const uint16_t* wt, uint16_t* ou
 // gives, and the most splits of the voxels: 512 workgroups, two on each CU
 int wgrad_blocks(const ULayer& l) { return l.co == 16 && (l.ci + 15) / 16 == 3 ? 3 : 1; }
 int wgrad_rows(const ULayer& l) { return (l.ci + 15) / 16 / wgrad_blocks(l); }
-int wgrad_splits(const ULayer& l) { return 512 / wgrad_rows(l); }
+int wgrad_splits(const ULayer& l, int E) {
+  const int tiles = ((E + kTX - 1) / kTX) * ((E + kTY - 1) / kTY) * ((E + kTZ - 1) / kTZ);
+  return std::min(tiles, 512 / wgrad_rows(l));
+}
 
-int wgrad(UNet& u, int layer, const uint16_t* in, int cs_in, const uint16_t* dy, int cs_dy, int E, float scale,
+int wgrad(UNet& u, float* partial, int layer, const uint16_t* in, int cs_in, const uint16_t* dy, int cs_dy, int E, float scale,
           int accumulate, hipStream_t s) {
   const ULayer& l = u.L[layer];
   const int MB = (l.ci + 15) / 16, NB = l.co / 16;
-  const int tiles = ((E + kTX - 1) / kTX) * ((E + kTY - 1) / kTY) * ((E + kTZ - 1) / kTZ);
-  const int S = std::min(tiles, wgrad_splits(l));
+  const int S = wgrad_splits(l, E);
   const dim3 g((unsigned)S, (unsigned)wgrad_rows(l));
-#define WG(a, b) k_wgrad<a, b><<<g, 256, 0, s>>>(in, cs_in, l.ci, dy, cs_dy, E, S, u.partial, MB * 16)
+#define WG(a, b) k_wgrad<a, b><<<g, 256, 0, s>>>(in, cs_in, l.ci, dy, cs_dy, E, S, partial, MB * 16)
   switch (wgrad_blocks(l) * 10 + NB) {
     case 11: WG(1, 1); break;
     case 12: WG(1, 2); break;
@@ -1158,7 +1160,7 @@ int wgrad(UNet& u, int layer, const uint16_t* in, int cs_in, const uint16_t* dy,
 #undef WG
   CHNS_HIP(hipGetLastError());
   const int n = 27 * l.ci * l.co;
-  k_wgrad_reduce<<<(n + 63) / 64, 1024, 0, s>>>(u.partial, S, l.ci, l.co, MB * 16, NB * 16, u.grad + l.off, scale,
+  k_wgrad_reduce<<<(n + 63) / 64, 1024, 0, s>>>(partial, S, l.ci, l.co, MB * 16, NB * 16, u.grad + l.off, scale,
                                                 accumulate);
   CHNS_HIP(hipGetLastError());
   return CHNS_OK;
@@ -1220,9 +1222,13 @@ int ensure_acts(Ctx& c, int E, bool grads, UActs** out) {
     a.target = F(V0);
     a.mask = F(V0);
     a.dout = F(V0);
+    size_t np = 0;
+    for (int k = 0; k < kLayers; ++k)
+      np = std::max(np, (size_t)wgrad_splits(u.L[k], E >> kLevel[k]) * 27 * ((u.L[k].ci + 15) / 16 * 16) * u.L[k].co);
+    a.partial = F((int64_t)np);
     if (!a.dA13 || !a.dA12 || !a.dcat0 || !a.dA11 || !a.dA10 || !a.dcat1 || !a.dA9 || !a.dA8 || !a.dcat2 ||
         !a.dA7 || !a.dA6 || !a.dP2 || !a.dA4 || !a.dP1 || !a.dA2 || !a.dP0 || !a.dA0 || !a.target || !a.mask ||
-        !a.dout)
+        !a.dout || !a.partial)
       return CHNS_ENOMEM;
   }
   u.acts.push_back(a);
@@ -1283,7 +1289,7 @@ int backward(UNet& u, UActs& a, float scale, int accumulate, hipStream_t s) {
                    uint16_t* dx, int cs_dx, int E, int64_t V) -> int {
     k_relu_bwd<<<nblk(V * L[k].co / 8), kT, 0, s>>>(dy, cs_dy, act, cs_act, L[k].co, V);
     CHNS_HIP(hipGetLastError());
-    int e = wgrad(u, k, in, cs_in, dy, cs_dy, E, scale, accumulate, s);
+    int e = wgrad(u, a.partial, k, in, cs_in, dy, cs_dy, E, scale, accumulate, s);
     if (e) return e;
     if (dx) return conv(dy, cs_dy, L[k].co, L[k].wb, dx, cs_dx, L[k].ci, E, false, s);
     return CHNS_OK;
@@ -1393,15 +1399,10 @@ int unet_create(Ctx& c) {
   u.v = (float*)c.dalloc(sizeof(float) * u.nparam);
   u.grad = (float*)c.dalloc(sizeof(float) * u.nparam);
   u.wbf = (uint16_t*)c.dalloc(sizeof(uint16_t) * nbf);
-  size_t pmax = 0;
-  for (int k = 0; k < kLayers; ++k)
-    pmax = std::max(pmax, (size_t)wgrad_splits(u.L[k]) * 27 * ((u.L[k].ci + 15) / 16 * 16) * u.L[k].co);
-  u.partial = (float*)c.dalloc(sizeof(float) * pmax);
-  u.partial_cap = pmax;
   u.red = (double*)c.dalloc(sizeof(double) * 3 * kRedBlocks);  // up to three partial rows
   u.scal = (double*)c.dalloc(sizeof(double) * 16);
   u.gout_part = (float*)c.dalloc(sizeof(float) * 16 * kRedBlocks);
-  if (!u.W || !u.m || !u.v || !u.grad || !u.wbf || !u.partial || !u.red || !u.scal || !u.gout_part)
+  if (!u.W || !u.m || !u.v || !u.grad || !u.wbf || !u.red || !u.scal || !u.gout_part)
     return CHNS_ENOMEM;
   CHNS_HIP(hipHostMalloc((void**)&u.scal_host, sizeof(double) * 16, hipHostMallocDefault));
   size_t b = 0;
