@@ -230,7 +230,6 @@ template <typename T>
 struct BrickArgs {
   const int32_t* table;
   const int8_t* level;
-  const int16_t* rank;
   int64_t count;
   int64_t slot_base;
   int nbnd;
@@ -607,13 +606,13 @@ __device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int 
 // column).  In units of the transformed values a gradient is gamma times the
 // transformed difference, gamma = (2/h)/(2 w), and the same factor stands in
 // front of a gradient test function, so b and k are stored as gamma b and
-// gamma^2 k and the weight det J w^2d goes into rho, k and grad eta~;
-// the test functions are applied by the same transforms
-// transposed.  The coefficients are formed once per Gauss point (the phase
-// field clamped, tau_m, b scaled by 2/h, grad phi~ per column with the
-// pull-back mask per point), then each component is transformed, combined
-// and handed to out(f, y) in turn.  cv(f, a): f < DIM the velocity
-// components, then phi~ (stored as in PhaseT), mu~, u^.
+// gamma^2 k and the weight det J w^2d goes into rho, k and grad eta~; the
+// test functions are applied by the same transforms transposed.  The
+// coefficients are formed once per Gauss point (the phase field clamped,
+// tau_m, b scaled by 2/h, grad phi~ per column with the pull-back mask per
+// point), then each component is transformed, combined and handed to
+// out(f, y) in turn.  cv(f, a): f < DIM the velocity components, then phi~
+// (phi in FP64, 1 + phi in FP32), mu~, u^.
 template <int DIM, typename T, class CV, class OUT>
 __device__ __forceinline__ void el_vp(const CV& cv, const FormConst<T>& K, int lev, const OUT& out) {
   constexpr int NC = 1 << DIM, H = NC / 2;
@@ -2128,11 +2127,11 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   hipEvent_t ev;
   // uniform meshes in one kernel, no slots and no combine: every 2D form (the
   // right-hand sides from 64^2 leaves) and the 3D pressure operator in FP64.
-  // In FP32 that operator keeps the bricks and their order of sums, so that it
-  // gives the same bits as the brick path of an octree with the same leaves:
-  // refinement around restarted FP32 solves turns a change of rounding into a
-  // few iterations (327 to 338 for the learned preconditioner at 128^3), and
-  // the two paths agree exactly.
+  // In FP32 that operator keeps the bricks and their order of sums: it gives
+  // the same bits as the brick path of an octree with the same leaves, so the
+  // learned preconditioner's solves through the node grid and on the uniform
+  // mesh take the same iterations (another order moves them by a few, either
+  // way).  The price: 25 us at 128^3, where the FP64 kernel takes 23.
   constexpr bool TILE3 = DIM == 3 && OP == K_PP && sizeof(T) == 8;
   const bool whole = dm.structured && (DIM == 2 || TILE3) && OP != K_DIAG && !rhs_on_bricks<DIM, OP>(dm.side);
   const int tx2 = std::max(1, (dm.side - 1 + kTile2X - 1) / kTile2X);

@@ -30,7 +30,6 @@ struct DevBrickClass {
   int64_t slot_base = 0;
   int32_t* table = nullptr;
   int8_t* level = nullptr;
-  int16_t* rank = nullptr;  // npb entries
   int32_t* anchor = nullptr;  // 3 per brick (integer node coordinates)
   int32_t* abase = nullptr;   // 8 per brick, or null (see BrickClass::abase)
 };

@@ -591,12 +591,12 @@ __global__ void k_stencil_dense(const double* __restrict__ S, int s, double* M) 
 // sum_o S_o(i) v(i + off_o) on a uniform level (zero stencil entries reach
 // no node outside the level; their indices are skipped)
 //
-// Index of the neighbour at offset (ox, oy, oz), clamped into the level: the
-// stencil value of an offset outside the level is 0, so every load can be
-// unconditional (all issued at once) and the sum is the same.
 // keeps the loads before it in flight together: left alone, the compiler sinks
 // each to its use
 __device__ __forceinline__ void load_fence() { asm volatile("" ::: "memory"); }
+// Index of the neighbour at offset (ox, oy, oz), clamped into the level: the
+// stencil value of an offset outside the level is 0, so every load can be
+// unconditional (all issued at once) and the sum is the same.
 template <int DIM>
 __device__ __forceinline__ int nbr(int node, int ox, int oy, int oz, int s1, int n) {
   return min(max(node + ox + oy * s1 + (DIM == 3 ? oz * s1 * s1 : 0), 0), n - 1);
@@ -882,8 +882,6 @@ int upload_dm(Ctx& c, const HostMesh& m, DevMesh& d) {
     b.slot_base = h.slot_base;
     if ((rc = upload(c, &b.table, h.table))) return rc;
     if ((rc = upload(c, &b.level, h.level))) return rc;
-    std::vector<int16_t> r(h.rank.begin(), h.rank.end());
-    if ((rc = upload(c, &b.rank, r))) return rc;
     if ((rc = upload(c, &b.anchor, h.anchor))) return rc;
     if (!h.abase.empty() && (rc = upload(c, &b.abase, h.abase))) return rc;
   }
