@@ -50,11 +50,6 @@ __device__ __forceinline__ double rsqrt_t(double x) {
   return __builtin_fma(0.5 * y, e, y);
 }
 __device__ __forceinline__ float rsqrt_t(float x) { return __builtin_amdgcn_rsqf(x); }
-// Pull back of the (scaled) phase field to its physical range.  FP64 fields
-// hold phi in [-lim, lim]; FP32 fields hold 1 + phi in [0, 2 lim].
-__device__ __forceinline__ double clamp_t(double v, double lim) { return fmin(fmax(v, -lim), lim); }
-__device__ __forceinline__ float clamp_t(float v, float lim) { return __builtin_amdgcn_fmed3f(v, 0.0f, 2.0f * lim); }
-
 // fused multiply-add in the operands' own precision (__builtin_fma is the
 // double one: float operands would be widened and the result narrowed)
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
@@ -79,6 +74,42 @@ template <int N>
 constexpr double kWp = march::kW * kWp<N - 1>;
 template <>
 inline constexpr double kWp<0> = 1.0;
+// A constant with its rounding to T beside it.  An FP32 constant is off by up
+// to 2^-25, the same for every leaf: where the constant only scales values, a
+// bias of the whole result (the Cahn-Hilliard Jacobian at 32^3 leaves was 7.3e-8
+// from 64 bits with plain constants, 6.0e-8 with these).
+template <typename T>
+struct Const2 {
+  T hi, lo;
+};
+template <typename T>
+__host__ __device__ constexpr Const2<T> const2(double v) {
+  return {T(v), T(v - (double)T(v))};
+}
+// times 2^e
+template <typename T>
+__device__ __forceinline__ Const2<T> scaled(Const2<T> c, int e) {
+  return {T(ldexp(c.hi, e)), T(ldexp(c.lo, e))};
+}
+__device__ __forceinline__ double times(double v, Const2<double> c) { return v * c.hi; }
+__device__ __forceinline__ float times(float v, Const2<float> c) { return fma_t(v, c.hi, v * c.lo); }
+
+// Phase field of the mixture laws: s = (1 + phi)/2, its pull back a clamp to
+// [0, 1], rho = rho- + (rho+ - rho-) s.  The stored field (FP64 phi, FP32 1 +
+// phi) becomes w^d s at the corners, before the transforms, so that the light
+// phase, s = 0, is held exactly; taken from phi after them, rho- came out of a
+// difference of two rounded halves, and the 2D pressure apply at density ratio
+// 1000 on 64^2 leaves was 6.7e-14 from 64 bits instead of 2.7e-14.
+template <int DIM>
+__device__ __forceinline__ double phase_s(double v) {
+  constexpr double k = 0.5 * kWp<DIM>;
+  return __builtin_fma(v, k, k);
+}
+template <int DIM>
+__device__ __forceinline__ float phase_s(float v) {
+  return times(v, const2<float>(0.5 * kWp<DIM>));
+}
+
 template <int N, int BIT, typename T>
 __device__ __forceinline__ void stage(T* v) {
 #pragma unroll
@@ -106,12 +137,12 @@ template <int DIM, typename T, bool RCP = true>
 __device__ __forceinline__ void elem_pp_coef(const T* ph, T A, T Bc, T* c) {
   constexpr int NC = 1 << DIM;
 #pragma unroll
-  for (int i = 0; i < NC; ++i) c[i] = ph[i];
+  for (int i = 0; i < NC; ++i) c[i] = phase_s<DIM>(ph[i]);
   all_stages<DIM>(c);
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
-    // coefficient 1 / (A phi + B) (pressure) or A phi + B (viscosity)
-    const T lin = fma_t(A, clamp_t(c[i], T(1.0 / kWp<DIM>)), Bc);
+    // coefficient 1 / (A s + B) (pressure) or A s + B (viscosity)
+    const T lin = fma_t(A, march::sat(c[i]), Bc);
     c[i] = RCP ? rcp_t(lin) : lin;
   }
 }
@@ -159,10 +190,10 @@ __device__ __forceinline__ void elem_mass_coef(const T* ph, T A, T Bc, T* r) {
   constexpr int NC = 1 << DIM;
   if constexpr (RHO) {
 #pragma unroll
-    for (int i = 0; i < NC; ++i) r[i] = ph[i];
+    for (int i = 0; i < NC; ++i) r[i] = phase_s<DIM>(ph[i]);
     all_stages<DIM>(r);
 #pragma unroll
-    for (int i = 0; i < NC; ++i) r[i] = fma_t(A, clamp_t(r[i], T(1.0 / kWp<DIM>)), Bc);
+    for (int i = 0; i < NC; ++i) r[i] = fma_t(A, march::sat(r[i]), Bc);
   } else {
 #pragma unroll
     for (int i = 0; i < NC; ++i) r[i] = Bc;
@@ -218,13 +249,13 @@ constexpr int kMaxCoef = kMaxCoefFields;
 template <typename T>
 struct FormConst {
   T idt;                     // 1 / dt
-  T kphi, kmu;               // Jacobian: stiffness of phi and mu over h^(d-2)
+  Const2<T> kphi, kmu;       // Jacobian: stiffness of phi and mu over h^(d-2)
   T ra, rb, rwa, rwb;        // momentum: rho = ra s + rb, the same times w^2d
   T kea, keb, cgp, cJ;       // gamma^2 k, grad eta~, gamma J / (2 Pe) (el_vp)
   T tau_c, va, vb, vc;       // 4 / dt^2, eta / Re = va s + vb, C_I d
 };
 template <int DIM, typename T>
-FormConst<T> form_const(const Phys& P);
+FormConst<T> form_const(const Phys& P, double rm, double em);
 
 template <typename T>
 struct BrickArgs {
@@ -241,9 +272,8 @@ struct BrickArgs {
   T* slots;
   const int32_t* hang;
   const uint8_t* wall;
-  double alpha, beta;  // rho(phi) = alpha phi + beta
-  double ratio;        // rho-/rho+
-  Phys phys;           // physical parameters of the CHNS forms
+  double ratio, eta_ratio;  // rho-/rho+, eta-/eta+
+  Phys phys;                // physical parameters of the CHNS forms
   double* partials;    // fused x.y partial per block, or null
   const int* done;
   // damped-Jacobi sweep (pressure operator): y = x + sm_w sm_d (sm_r - A x)
@@ -469,32 +499,30 @@ __device__ __forceinline__ void el_energy(const double (*c)[1 << DIM], const Phy
 // field is held in registers longer than it is used.
 //
 // Phase-field storage: FP64 fields hold phi, FP32 fields hold 1 + phi (so
-// that rho = (beta - alpha) + alpha (1 + phi) keeps its relative accuracy
-// near phi = -1 at large density ratios); the pull-back range and the mixture
-// laws rho = ra s + rb, eta = ea s + eb are in the stored variable s.
+// that rho keeps its relative accuracy near phi = -1 at large density ratios);
+// the mixture laws are rho = ra s + rb, eta = ea s + eb in s = (1 + phi)/2.
+// rm, em: rho-/rho+, eta-/eta+.
 template <int DIM, typename T>
-FormConst<T> form_const(const Phys& P) {
+FormConst<T> form_const(const Phys& P, double rm, double em) {
   constexpr double wd = kWp<DIM>, w2d = kWp<2 * DIM>, g1 = 1.0 / (2.0 * march::kW);  // gamma / (2/h)
-  const bool shifted = sizeof(T) == 4;
-  const double rb = shifted ? P.beta - P.alpha : P.beta, eb = shifted ? P.xi - P.gam : P.xi;
   const double st = DIM == 3 ? 1.0 / 12.0 : 1.0 / 6.0;
   FormConst<T> f;
   f.idt = T(1.0 / P.dt);
-  f.kphi = T(st * P.Cn * P.Cn * 0.5);
-  f.kmu = T(st / (2.0 * P.Pe * P.Cn));
-  f.ra = T(P.alpha);
-  f.rb = T(rb);
-  f.rwa = T(P.alpha * w2d);
-  f.rwb = T(rb * w2d);
+  f.kphi = const2<T>(st * P.Cn * P.Cn * 0.5);
+  f.kmu = const2<T>(st / (2.0 * P.Pe * P.Cn));
+  f.ra = T(1.0 - rm);
+  f.rb = T(rm);
+  f.rwa = T((1.0 - rm) * w2d);
+  f.rwb = T(rm * w2d);
   // gamma^2 k, gamma^2 w^d gam/(2 Re) (grad eta~ of a transformed column, one
   // gamma its own and one of grad v) and gamma J / (2 Pe), without their 2/h
-  f.kea = T(P.gam / (2.0 * P.Re) * (g1 * g1 * w2d));
-  f.keb = T(eb / (2.0 * P.Re) * (g1 * g1 * w2d));
+  f.kea = T((1.0 - em) / (2.0 * P.Re) * (g1 * g1 * w2d));
+  f.keb = T(em / (2.0 * P.Re) * (g1 * g1 * w2d));
   f.cgp = T(P.gam / (2.0 * P.Re) * (wd * g1 * g1 * w2d));
   f.cJ = T(P.cJ * (wd * g1 * g1) / (2.0 * P.Pe));
   f.tau_c = T(4.0 / (P.dt * P.dt));
-  f.va = T(P.gam / P.Re);
-  f.vb = T(eb / P.Re);
+  f.va = T((1.0 - em) / P.Re);
+  f.vb = T(em / P.Re);
   f.vc = T(P.C_I * DIM);
   return f;
 }
@@ -512,8 +540,8 @@ template <int DIM, typename T, class CV>
 __device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int lev, T (*y)[1 << DIM]) {
   constexpr int NC = 1 << DIM, H = NC / 2;
   // the w^d of a transform and of its transpose folded into the weight
-  const T w = T(ldexp(kWp<2 * DIM>, -(lev + 1) * DIM));
-  const T wd = T(kWp<DIM>);
+  const Const2<T> w = scaled(const2<T>(kWp<2 * DIM>), -(lev + 1) * DIM);
+  constexpr Const2<T> wd = const2<T>(kWp<DIM>);
   // stiffness parts, corner form
   {
     T xp[NC], xm[NC];
@@ -522,7 +550,7 @@ __device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int 
       xp[a] = cv(0, a);
       xm[a] = cv(1, a);
     }
-    const T kphi = ldexp(K.kphi, -lev * (DIM - 2)), kmu = ldexp(K.kmu, -lev * (DIM - 2));
+    const Const2<T> kphi = scaled(K.kphi, -lev * (DIM - 2)), kmu = scaled(K.kmu, -lev * (DIM - 2));
     T sp = T(0), sm = T(0);
 #pragma unroll
     for (int a = 0; a < NC; ++a) {
@@ -539,8 +567,8 @@ __device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int 
         kp = T(4) * xp[a] - (xp[a ^ 1] + xp[a ^ 2]) - T(2) * xp[a ^ 3];
         km = T(4) * xm[a] - (xm[a ^ 1] + xm[a ^ 2]) - T(2) * xm[a ^ 3];
       }
-      y[0][a] = kmu * km;
-      y[1][a] = kphi * kp;
+      y[0][a] = times(km, kmu);
+      y[1][a] = times(kp, kphi);
     }
     // mass parts at the Gauss points (values scaled by w^-d)
     all_stages<DIM>(xp);
@@ -550,13 +578,13 @@ __device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int 
     for (int a = 0; a < NC; ++a) pt[a] = cv(2, a);
     all_stages<DIM>(pt);
     T fa[NC], fb[NC];
-    const T wi = w * K.idt;
+    const Const2<T> wi{w.hi * K.idt, w.lo * K.idt}, wh{w.hi * T(0.5), w.lo * T(0.5)};
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      const T p = pt[q] * wd;
+      const T p = times(pt[q], wd);
       const T d2 = T(3) * p * p - T(1);
-      fa[q] = wi * xp[q];
-      fb[q] = w * T(0.5) * (d2 * xp[q] - xm[q]);
+      fa[q] = times(xp[q], wi);
+      fb[q] = times(d2 * xp[q] - xm[q], wh);
     }
     all_stages<DIM>(fa);
     all_stages<DIM>(fb);
@@ -567,7 +595,7 @@ __device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int 
     }
     // advection -1/2 (grad q, u~ dphi): flux F_d = -1/2 det J u~_d dphi at
     // each Gauss point, then the transposed gradient (constant along d)
-    const T wa = T(-0.5 * ldexp(kWp<3 * DIM - 1>, -(lev + 1) * DIM + lev));
+    const Const2<T> wa = scaled(const2<T>(-0.5 * kWp<3 * DIM - 1>), -(lev + 1) * DIM + lev);
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
       T u[NC];
@@ -585,7 +613,7 @@ __device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int 
 #pragma unroll
       for (int r = 0; r < H; ++r) {
         const int lo = insert0(r, d), hi = lo | (1 << d);
-        const T v = wa * g[r];
+        const T v = times(g[r], wa);
         y[0][hi] += v;
         y[0][lo] -= v;
       }
@@ -616,13 +644,11 @@ __device__ __forceinline__ void el_chj(const CV& cv, const FormConst<T>& K, int 
 template <int DIM, typename T, class CV, class OUT>
 __device__ __forceinline__ void el_vp(const CV& cv, const FormConst<T>& K, int lev, const OUT& out) {
   constexpr int NC = 1 << DIM, H = NC / 2;
-  // range of the stored phase field (phi* in [-1, 1])
-  constexpr T lo_s = sizeof(T) == 4 ? T(0) : T(-1), hi_s = sizeof(T) == 4 ? T(2) : T(1);
   // powers of two (2/h = 2^e1, det J = 2^-d e1) are applied with ldexp: exact,
   // and no per-level constants held in registers
   const int e1 = lev + 1;
   constexpr double g1 = 1.0 / (2.0 * march::kW);  // gamma / (2/h)
-  const T iSt = T(kWp<DIM>);
+  constexpr Const2<T> iS = const2<T>(kWp<DIM>), hg = const2<T>(0.5 * g1);
 
   // ---- coefficients at the Gauss points
   T sc[NC], tau[NC], bs[DIM][NC], gp[DIM][H];
@@ -643,12 +669,13 @@ __device__ __forceinline__ void el_vp(const CV& cv, const FormConst<T>& K, int l
 #pragma unroll
       for (int r = 0; r < H; ++r) gp[d][r] = ldexp(gp[d][r] * K.cgp, 2 * e1);
     }
+#pragma unroll
+    for (int a = 0; a < NC; ++a) v[a] = phase_s<DIM>(v[a]);
     all_stages<DIM>(v);
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
-      const T s = v[q] * iSt;
-      sc[q] = fmin(fmax(s, lo_s), hi_s);
-      if (s > lo_s && s < hi_s) inside |= 1u << q;
+      sc[q] = march::sat(v[q]);
+      if (v[q] > T(0) && v[q] < T(1)) inside |= 1u << q;
     }
   }
   asm volatile("" ::: "memory");
@@ -687,11 +714,11 @@ __device__ __forceinline__ void el_vp(const CV& cv, const FormConst<T>& K, int l
 #pragma unroll
       for (int q = 0; q < NC; ++q) {
         const int r = (q & ((1 << d) - 1)) | ((q >> (d + 1)) << d);
-        const T uh = u[q] * iSt;
+        const T uh = times(u[q], iS);
         const T j2 = J[d][r];  // gamma J / (2 Pe) over 2/h
         uu[q] = fma_t(uh, uh, uu[q]);
         uJ[q] = fma_t(uh, j2, uJ[q]);
-        bs[d][q] = ldexp(fma_t(j2, irho[q], T(0.5 * g1) * uh), e1);
+        bs[d][q] = ldexp(fma_t(j2, irho[q], times(uh, hg)), e1);
       }
     }
 #pragma unroll
@@ -788,36 +815,33 @@ struct OpConst {
 };
 template <int DIM, typename T, int OP>
 __device__ __forceinline__ OpConst<T> op_const(const BrickArgs<T>& a, int lev) {
-  // FP32 fields carry 1 + phi, so rho = (beta - alpha) + alpha (1 + phi)
-  const double beta0 = sizeof(T) == 8 ? a.beta : a.beta - a.alpha;
+  // rho = rho- + (rho+ - rho-) s and eta likewise, over rho+ and eta+
+  const double ra = 1.0 - a.ratio, rb = a.ratio;
   OpConst<T> o;
   o.gs = ldexp(1.0, lev + 1);
   o.wdet = ldexp(1.0, -(lev + 1) * DIM);
-  // mass: det J w^2d; stiffness: (h/2)^(d-2) / 4 w^2(d-1); phi: w^d
+  // mass: det J w^2d; stiffness: (h/2)^(d-2) / 4 w^2(d-1)
   const double mass = ldexp(kWp<2 * DIM>, -(lev + 1) * DIM);
   const double F = ldexp(kWp<2 * (DIM - 1)> / 4.0, -(lev + 1) * (DIM - 2));
-  constexpr double wd = kWp<DIM>;
   if constexpr (OP == K_PPS) o.Ms = T(a.shift * mass);
   if constexpr (OP == K_VPS) {
-    // viscosity eta/(2 Re) = (gam phi + xi)/(2 Re) on the stiffness (folded
-    // like the pressure coefficient, without the reciprocal) and rho/dt on
-    // the mass
-    const double g2 = a.phys.gam / (2.0 * a.phys.Re), x2 = a.phys.xi / (2.0 * a.phys.Re);
-    o.A = T(g2 * F * wd);
-    o.Bc = T((sizeof(T) == 8 ? x2 : x2 - g2) * F);
-    o.Am = T(a.alpha / a.phys.dt * mass * wd);
-    o.Bm = T(beta0 / a.phys.dt * mass);
+    // viscosity eta/(2 Re) on the stiffness (folded like the pressure
+    // coefficient, without the reciprocal) and rho/dt on the mass
+    o.A = T((1.0 - a.eta_ratio) / (2.0 * a.phys.Re) * F);
+    o.Bc = T(a.eta_ratio / (2.0 * a.phys.Re) * F);
+    o.Am = T(ra / a.phys.dt * mass);
+    o.Bm = T(rb / a.phys.dt * mass);
   }
   if constexpr (OP == K_PP || OP == K_PPS) {
     // c~ = F / rho = 1 / (rho / F)
     const double f = ldexp(4.0 / kWp<2 * (DIM - 1)>, (lev + 1) * (DIM - 2));
-    o.A = T(a.alpha * f * wd);
-    o.Bc = T(beta0 * f);
+    o.A = T(ra * f);
+    o.Bc = T(rb * f);
   } else if constexpr (OP == K_MASS) {
     o.Bc = T(mass);
   } else if constexpr (OP == K_MASS_RHO) {
-    o.A = T(a.alpha * mass * wd);
-    o.Bc = T(beta0 * mass);
+    o.A = T(ra * mass);
+    o.Bc = T(rb * mass);
   }
   return o;
 }
@@ -2109,15 +2133,14 @@ int apply_t(Ctx& c, const LevelView& L, const T* x, T* y, const T* const* cf, hi
   a.hang = dm.hang_par;
   a.wall = dm.wall;
   a.phys = phys_of(c.prm);
-  a.alpha = a.phys.alpha;
-  a.beta = a.phys.beta;
   a.ratio = c.prm.rho_minus / c.prm.rho_plus;
+  a.eta_ratio = c.prm.eta_minus / c.prm.eta_plus;
   a.done = o.done;
   a.sm_r = (const T*)o.sm_r;
   a.sm_d = (const T*)o.sm_dinv;
   a.sm_w = (T)o.sm_w;
   a.shift = c.pp_shift;
-  if constexpr (OP == K_CH_JAC || OP == K_VP) a.fc = form_const<DIM, T>(a.phys);
+  if constexpr (OP == K_CH_JAC || OP == K_VP) a.fc = form_const<DIM, T>(a.phys, a.ratio, a.eta_ratio);
   a.diag_of = o.diag_of;
   a.sy = dm.side + 1;
   a.sz = (int64_t)(dm.side + 1) * (dm.side + 1);
