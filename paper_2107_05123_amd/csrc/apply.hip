@@ -1912,28 +1912,42 @@ __global__ void k_take_block(double* blk, const double* y, const uint8_t* color,
 // long chunks do less work and short ones fill the chip; `fill` blocks are
 // enough (measured minimum of the chunk sweeps at 16 to 256 leaves per edge
 // in 3D, where chunks below three layers only pay while the chip is not full).
-// Chunks of one row or layer as long as there are at most `one` of them.
-int chunk_own(int64_t tiles, int side, int64_t fill, int64_t one, int least) {
-  if (tiles * (side + 1) <= one) return 1;
+int chunk_own(int64_t tiles, int side, int64_t fill, int least) {
+  if (tiles * (side + 1) <= fill / 3) return 1;
   return (int)std::max<int64_t>(least, (tiles * (side + 1) + fill - 1) / fill);
 }
 
 int64_t tile3_columns(int side) {
   return (int64_t)((side + kTileX - 1) / kTileX) * ((side + kTileY - 1) / kTileY);
 }
-int tile3_own(int side) { return chunk_own(tile3_columns(side), side, 1536, 512, 3); }
+int tile3_own(int side) { return chunk_own(tile3_columns(side), side, 1536, 3); }
 // the right-hand sides: every register of a SIMD, so one wave on each of the
 // 1,024
 template <int OP>
 constexpr bool is_rhs() {
   return OP == K_VP_RHS || OP == K_PP_RHS || OP == K_VU_RHS;
 }
-// 2D: a right-hand side has room for 1,024 blocks at once, and more would run
-// in a second round (the pressure's at 256^2 leaves 21.1 -> 16.3 us, at 1024^2
-// 110 -> 89, as much as the bricks took)
+// 2D: blocks of a right-hand side run in rounds of 1,024, so its chunks are
+// those with the fewest rows to march in all rounds, the row below each chunk
+// counted (against 6,144 blocks, the pressure's: 256^2 leaves 21.4 -> 16.4 us,
+// 512^2 44.6 -> 31.2, 1024^2 110 -> 89, 8192^2 5.26 -> 4.80 ms; the bricks take
+// 39.5, 41.1, 86 us and 5.23 ms)
 template <int OP>
 int tile2_own(int tiles, int side) {
-  return is_rhs<OP>() ? chunk_own(tiles, side, 1024, 1024, 2) : chunk_own(tiles, side, 6144, 2048, 2);
+  if (!is_rhs<OP>()) return chunk_own(tiles, side, 6144, 2);
+  constexpr int kSlots = 1024, kRounds = 8;
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int r = 1; r <= kRounds; ++r) {
+    const int chunks = std::min(std::max(1, r * kSlots / tiles), side + 1), own = (side + chunks) / chunks;
+    const int64_t blocks = (int64_t)tiles * ((side + own) / own);
+    const int64_t rows = (blocks + kSlots - 1) / kSlots * (own + 1);
+    if (rows < least) {
+      least = rows;
+      best = own;
+    }
+  }
+  return best;
 }
 // ... and on at most 32^2 leaves stays on the bricks: there a wave's two leaf
 // rows take longer than one leaf of a brick and the combine (10.3 us against

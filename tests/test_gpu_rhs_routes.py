@@ -9,7 +9,8 @@ the sums in another order only: 1e-12 relative (2-norm and max-norm).
 
 Uniform 2D meshes against the oracle at the sides where the route or the chunk
 length changes: 8^2 and 32^2 leaves (bricks), 64^2 (one row a wave; the brick
-tests hold it too) and 256^2 (two rows a wave, the last chunk shorter).
+tests hold it too), 256^2 (two rows a wave, the last chunk shorter) and 512^2
+(five rows, nine tiles).
 """
 import numpy as np
 import pytest
@@ -24,7 +25,7 @@ pytestmark = pytest.mark.gpu
 
 # (id, kind, dim, lmin, lmax, radius, band, Cn, brick classes)
 CASES = [(f"uniform2d_l{lev}", "uniform", 2, lev, lev, 0.15, 0.03, cn, ())
-         for lev, cn in ((3, 0.1), (5, 0.04), (6, 0.02), (8, 0.01))]
+         for lev, cn in ((3, 0.1), (5, 0.04), (6, 0.02), (8, 0.01), (9, 0.01))]
 
 
 @pytest.fixture(scope="module", params=CASES, ids=lambda c: c[0])
